@@ -211,6 +211,8 @@ struct Params {
 constexpr int BAR_WORDS = 9216 + 64 * 32 * 32;
 
 hipError_t launch_block(const Params& p, int blocks, int threads, hipStream_t s);
+// Params::mode 1: one rate solve per part, one workgroup per part.
+hipError_t launch_solve(const Params& p, int blocks, int threads, hipStream_t s);
 hipError_t launch_grid(const Params& p, int blocks, int threads, hipStream_t s);
 // Largest co-resident grid for launch_grid at `threads` per block.
 hipError_t grid_capacity(int device, int threads, int* blocks);

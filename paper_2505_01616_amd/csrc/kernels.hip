@@ -2319,10 +2319,9 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
   }
 }
 
-template <class G>
-__device__ __forceinline__ void solve_only(G& g, const Params& P, const int sc, SolveLds* S,
+template <class G, class LK>
+__device__ __forceinline__ void solve_only(G& g, const Params& P, LK& lk, const int sc, SolveLds* S,
                                            Tally* tl, const FlowCache& fc) {
-  LinksGlobal lk{P.lst, P.nact, P.fl, P.inv_scale};
   ScenCtl* C = &P.ctl[sc];
   const int f0 = C->f0;
   if (threadIdx.x == 0) tl->rounds = tl->fsw = 0;
@@ -2376,19 +2375,60 @@ __global__ __launch_bounds__(NT) void netsim_block_kernel(Params P) {
     if (threadIdx.x == 0) lists = Lists{};
     __syncthreads();
     const int nl = C->l1 - C->l0;
-    const bool in_lds = P.mode == 0 && link_pool_bytes(nl) <= POOL_BYTES;
+    const bool in_lds = link_pool_bytes(nl) <= POOL_BYTES;
     const int used = in_lds ? (link_pool_bytes(nl) + 15) & ~15 : 0;
     const int ncache = (POOL_BYTES - used) / FLOW_LDS_BYTES;
     const FlowCache fc{reinterpret_cast<uint4*>(pool + used),
                        reinterpret_cast<int32_t*>(pool + used + 16 * ncache), ncache};
-    if (P.mode != 0) {
-      solve_only(g, P, sc, nullptr, &tally, fc);
-    } else if (in_lds) {
+    if (in_lds) {
       LinksShared lk(pool, C->l0, nl, P.inv_scale);
       event_loop<true>(g, P, lk, sc, nullptr, &tally, fc);
     } else {
       LinksGlobal lk{P.lst, P.nact, P.fl, P.inv_scale};
       event_loop<true>(g, P, lk, sc, nullptr, &tally, fc);
+    }
+    __syncthreads();
+  }
+}
+
+// One rate solve per part (no event loop), one workgroup per part.  The link
+// state of a part whose links fit is read into shared memory first (the
+// first freezing round alone gathers six links per flow), as in the block
+// kernel; the rounds are bound by the latency of those gathers and of the
+// freezing atomics.  A kernel of its own: next to the event loop's code the
+// solve's 1024-thread build spills 140 registers (6 here).  258,048 flows over
+// 20,480 links in eight parts: 2.06 ms (links in global memory, inside the
+// block kernel: 5.6 ms).
+template <int NT>
+__global__ __launch_bounds__(NT) void netsim_solve_kernel(Params P) {
+  __shared__ double lds[32];
+  __shared__ int ldsi[128];
+  __shared__ Tally tally;
+  __shared__ Lists lists;
+  __shared__ __align__(16) unsigned char pool[POOL_BYTES];
+  BlockG g{lds, ldsi, &lists};
+  for (int sc = blockIdx.x; sc < P.num_scen; sc += gridDim.x) {
+    const ScenCtl* C = &P.ctl[sc];
+    if (threadIdx.x == 0) lists = Lists{};
+    const int nl = C->l1 - C->l0;
+    const bool in_lds = link_pool_bytes(nl) <= POOL_BYTES;
+    const int used = in_lds ? (link_pool_bytes(nl) + 15) & ~15 : 0;
+    const int ncache = (POOL_BYTES - used) / FLOW_LDS_BYTES;
+    const FlowCache fc{reinterpret_cast<uint4*>(pool + used),
+                       reinterpret_cast<int32_t*>(pool + used + 16 * ncache), ncache};
+    if (in_lds && C->n_solve > 0) {
+      LinksShared lk(pool, C->l0, nl, P.inv_scale);
+      for (int l = C->l0 + (int)threadIdx.x; l < C->l1; l += blockDim.x) {
+        lk.reset(l, P.R0[l]);
+        lk.nact[l - C->l0] = P.nact[l];
+      }
+      if (threadIdx.x == 0) lk.set_sentinel(nl);
+      __syncthreads();
+      solve_only(g, P, lk, sc, nullptr, &tally, fc);
+    } else {
+      __syncthreads();
+      LinksGlobal lk{P.lst, P.nact, P.fl, P.inv_scale};
+      solve_only(g, P, lk, sc, nullptr, &tally, fc);
     }
     __syncthreads();
   }
@@ -2406,7 +2446,7 @@ __global__ __launch_bounds__(1024) void netsim_grid_kernel(Params P) {
   const FlowCache none{nullptr, nullptr, 0};
   for (int sc = 0; sc < P.num_scen; ++sc) {
     if (P.mode == 0) event_loop<true>(g, P, lk, sc, &S, &tally, none);
-    else solve_only(g, P, sc, &S, &tally, none);
+    else solve_only(g, P, lk, sc, &S, &tally, none);
     g.sync();
   }
 }
@@ -2518,6 +2558,14 @@ hipError_t launch_block(const Params& p, int blocks, int threads, hipStream_t s)
     hipLaunchKernelGGL(netsim_block_kernel<512>, dim3(blocks), dim3(threads), 0, s, p);
   else
     hipLaunchKernelGGL(netsim_block_kernel<1024>, dim3(blocks), dim3(threads), 0, s, p);
+  return hipGetLastError();
+}
+
+hipError_t launch_solve(const Params& p, int blocks, int threads, hipStream_t s) {
+  if (threads <= 512)
+    hipLaunchKernelGGL(netsim_solve_kernel<512>, dim3(blocks), dim3(threads), 0, s, p);
+  else
+    hipLaunchKernelGGL(netsim_solve_kernel<1024>, dim3(blocks), dim3(threads), 0, s, p);
   return hipGetLastError();
 }
 

@@ -835,7 +835,8 @@ netsim_status launch(netsim_t* h, hipStream_t st, bool solve_only, float* ms, bo
       int threads = h->opt.block_threads > 0 ? h->opt.block_threads : widest > 16384 ? 1024 : 512;
       threads = std::max(64, std::min(1024, threads / 64 * 64));
       const int blocks = std::max(1, std::min<int32_t>(S, 1 << 20));
-      he = netsim_dev::launch_block(P, blocks, threads, st);
+      he = solve_only ? netsim_dev::launch_solve(P, blocks, threads, st)
+                      : netsim_dev::launch_block(P, blocks, threads, st);
     }
   }
   if (he == hipSuccess) he = hipEventRecord(e1, st);
