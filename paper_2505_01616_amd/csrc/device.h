@@ -87,6 +87,12 @@ struct ScenCtl {
   int64_t ticks[8];        // wall-clock ticks per phase (first thread of the group)
   int64_t dbg[4];          // debug checks (options.debug)
   Lists k;                 // list counters in global memory (grid layout)
+  // a part handed over by the wave kernel in the middle of an event: its
+  // completions and releases are settled (theta and the new flows in Params::arr
+  // kept), its rate solve is still to come.  Bit 0: so; bit 1: the active set
+  // changed.
+  int32_t mid;
+  int32_t mid_slots0, mid_narr;  // slots before the event's new flows, new flows
 };
 
 enum : int32_t {
@@ -203,16 +209,29 @@ struct Params {
   ScenCtl* ctl;            // [num_scen]
   uint32_t* bar;           // synchronisation words [BAR_WORDS] (layout in kernels.hip)
   uint64_t* slots;         // grid min-reduction slots [4]
+  // block layout.  Parts of a launch: list[0..n) with n = *pcount or, without
+  // one, num_list (list NULL: every part)
+  const int32_t* list;
+  const int32_t* pcount;
+  int32_t num_list;
+  int32_t hand;            // 1: the parts of this launch were handed over by the wave kernel
+  int32_t* hlist;          // parts handed over by the wave kernel [num_scen], *hcount of them
+  int32_t* hcount;
 };
 
 // Words of Params::bar, cleared before every launch: 9,216 words of
 // barrier, registration and cluster words, then the cluster helpers'
 // arrival lines (64 clusters x 32 lines of 32 words).
 constexpr int BAR_WORDS = 9216 + 64 * 32 * 32;
+constexpr int BAR_HAND = 50;  // parts the wave kernel has handed over (Params::hcount)
 
 hipError_t launch_block(const Params& p, int blocks, int threads, hipStream_t s);
 // Params::mode 1: one rate solve per part, one workgroup per part.
 hipError_t launch_solve(const Params& p, int blocks, int threads, hipStream_t s);
+// Parts list[0..parts) one wavefront each (wave.hip), with room for sc active and
+// pc pending flows in lds bytes of shared memory (wave_bytes of the largest part).
+hipError_t launch_wave(const Params& p, const int32_t* list, int parts, int sc, int pc, size_t lds, hipStream_t s);
+size_t wave_bytes(int nl, int nc, int sc, int pc);
 hipError_t launch_grid(const Params& p, int blocks, int threads, hipStream_t s);
 // Largest co-resident grid for launch_grid at `threads` per block.
 hipError_t grid_capacity(int device, int threads, int* blocks);

@@ -65,9 +65,12 @@ __device__ __forceinline__ double scalar(double v) {
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
 // ------------------------------------------------------------------ groups
-// TIGHT: built for 1024 threads, 128 registers per lane (see fresh()).
-template <bool TIGHT>
+// TIGHT: the cluster kernel's leader (see fresh()).  MID: the event loop
+// may start in the middle of an event (parts handed over by the wave kernel;
+// the 512-thread kernel takes them).
+template <bool TIGHT, bool MID>
 struct BlockG {
+  static constexpr bool kMid = MID;
   double* lds;
   int* ldsi;
   Lists* lst;  // list counters: shared memory (block kernel, zeroed when a part
@@ -76,9 +79,9 @@ struct BlockG {
   int t = (int)threadIdx.x;
   // The thread index as a value the compiler cannot see through: addresses
   // are computed again after it.  Hoisted out of the event loop they take
-  // more registers than a 1024-thread build has (186 spilled; 76 with this
-  // and scalar loop state); a 512-thread build has room for them and is 2%
-  // faster with them.
+  // more registers than the cluster kernel has (128 per lane; 186 spilled, 76
+  // with this and scalar loop state: 7% of the time of an all-to-all of 448
+  // GPUs); a 512-thread build has room for them and is 2% faster with them.
   __device__ __forceinline__ void fresh() {
     if constexpr (TIGHT) asm volatile("" : "+v"(t));
   }
@@ -140,6 +143,7 @@ __device__ __forceinline__ unsigned xcc_id() {
 }
 
 struct GridG {
+  static constexpr bool kMid = false;
   double* lds;
   int* ldsi;
   __device__ Lists* lists(ScenCtl* C) const { return &C->k; }
@@ -151,7 +155,7 @@ struct GridG {
   bool ab;        // block-uniform copy of *flag, refreshed at every barrier
   uint32_t xcc, mine, nx;  // this block's XCD, blocks on it, XCDs in use
   template <class T>
-  __device__ __forceinline__ T uni(T v) const { return scalar(v); }
+  __device__ __forceinline__ T uni(T v) const { return v; }
   __device__ int tid() const { return blockIdx.x * blockDim.x + threadIdx.x; }
   __device__ int block_base() const { return blockIdx.x * blockDim.x; }
   __device__ int nblocks() const { return gridDim.x; }
@@ -481,8 +485,8 @@ struct ClusterG {
 
 template <class G>
 __device__ __forceinline__ int local_id(const G&) { return (int)threadIdx.x; }
-template <bool TIGHT>
-__device__ __forceinline__ int local_id(const BlockG<TIGHT>& g) { return g.t; }
+template <bool TIGHT, bool MID>
+__device__ __forceinline__ int local_id(const BlockG<TIGHT, MID>& g) { return g.t; }
 
 template <class G> struct IsGrid { static constexpr bool value = false; };
 template <> struct IsGrid<GridG> { static constexpr bool value = true; };
@@ -1046,8 +1050,8 @@ __device__ __forceinline__ void for_items(uint64_t mask, uint64_t cmask, const F
 // re-solve's take-back is done while the records are gathered and the slots
 // are written as flows freeze.  Paths must fit the record (<= 6 links,
 // part-local ids below 0xFFFF); n <= 64*T.
-template <bool TIGHT, class LK>
-__device__ __forceinline__ int solve_mask(BlockG<TIGHT>& g, const Params& P, LK& lk, ScenCtl* C,
+template <bool TIGHT, bool MID, class LK>
+__device__ __forceinline__ int solve_mask(BlockG<TIGHT, MID>& g, const Params& P, LK& lk, ScenCtl* C,
                                           const int32_t* list, int n, int64_t& rounds, int64_t& fsw,
                                           int64_t& isw, Clock& clk, bool warm, const FlowCache& fc,
                                           const Resel* rs) {
@@ -1876,10 +1880,16 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
     if (tid == 0) lk.set_sentinel(C->l1 - C->l0);
   }
   const uint64_t INF_BITS = (uint64_t)__double_as_longlong(INF);
-  for (int c = C->c0 + tid; c < C->c0 + C->nc; c += T) P.theta[c] = INF_BITS;
+  // a part the wave kernel left between an event's releases and its solve
+  // (block kernel only) starts there, with that event's thetas
+  constexpr bool kMid = G::kMid;
+  bool mid = kMid && resume && (C->mid & 1) != 0;
+  if (!kMid || !mid)
+    for (int c = C->c0 + tid; c < C->c0 + C->nc; c += T) P.theta[c] = INF_BITS;
   double t = g.uni(resume ? C->t : 0.0);
   int64_t events = g.uni(resume ? C->events : (int64_t)0), isw = 0;
-  const int64_t events0 = events;
+  // the launch's limit counts the wave kernel's events too
+  const int64_t events0 = kMid && P.hand && resume ? events - C->launch_events : events;
   int ab = g.uni(resume ? C->ab : 0);          // slot buffer in use
   int nSlots = g.uni(resume ? C->nslots : 0);  // slots in use (flows or holes)
   int nPend = g.uni(resume ? C->npend : C->n_pend0);
@@ -1905,6 +1915,11 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
     if (tid == 0) {
       g.store(&K->slots, nSlots);
       g.store(&K->holes, C->holes);
+      if (kMid && mid) {
+        g.store(&K->pend[(e & 1) ^ 1], C->npend);
+        g.store(&K->arr, C->mid_narr);
+        g.store(&K->changed[e & 1], C->mid >> 1);
+      }
     }
   }
   g.sync();
@@ -1918,6 +1933,9 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
     const Slots sl = slots(ab);
     const int32_t* pendIn = pend(ib);
     int32_t* pendOut = pend(ob);
+    // slots at or above this one are activated in this event
+    const int slots0 = kMid && mid ? C->mid_slots0 : nSlots;
+    if (!kMid || !mid) {
     if (tid == 0) {
       g.store(&K->pend[ob], 0);
       g.store(&K->changed[ib], 0);
@@ -1972,7 +1990,6 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
     }
     events += 1;
     const double thr = tn * THR;
-    const int slots0 = nSlots;  // slots at or above this one are activated in this event
     int32_t* compOut = comp(q % 3);
     int32_t* compCnt = &K->comp[q % 3];
     if (tid == 0) g.store(&K->comp[(q + 1) % 3], 0);
@@ -2122,6 +2139,9 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
     clk.lap(1);
     if (g.aborted()) { status = ST_BARRIER; break; }
     if (g.uni(g.load(&K->fault)) != 0) { status = ST_OVERFLOW; break; }
+    }  // !mid
+    if constexpr (kMid) mid = false;
+    int err = 0;
     nSlots = g.uni(g.load(&K->slots));
     const int pNew = g.uni(g.load(&K->pend[ob]));
     const int live = nSlots - g.uni(g.load(&K->holes));
@@ -2239,7 +2259,7 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
             rc = ST_OVERFLOW;
           } else if (C->lds_paths && nSel <= LDS_FLOWS) {
             if (g.block_id() == 0) {
-              BlockG<true> b{g.lds, g.ldsi, &C->k};  // the grid's counters, in global memory
+              BlockG<false, false> b{g.lds, g.ldsi, &C->k};  // the grid's counters, in global memory
               const int r1 = solve_mask(b, P, lk, C, arrs, nSel, rounds, fsw, isw, clk, true, fc,
                                         nullptr);
               if (threadIdx.x == 0) g.store(&K->solve_rc, r1);
@@ -2356,6 +2376,7 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
     C->assisted = tl->asst;
     C->links_swept = (resume ? C->links_swept : 0) + g.load(&K->lsw);
     if constexpr (HIST) C->hpos = hp;
+    if constexpr (kMid) C->mid = 0;
     C->launch_events = events - events0;
     C->status = status;
     for (int k = 0; k < 8; ++k) C->ticks[k] = (int64_t)tl->clk[k];
@@ -2401,10 +2422,11 @@ __device__ __forceinline__ void solve_only(G& g, const Params& P, LK& lk, const 
 
 }  // namespace
 
-// One workgroup per part.  A part whose links fit keeps its link state in
-// shared memory for the whole run; the rest of the pool caches the path
-// records of the flows being solved.  Built for workgroups of up to 512
-// threads (256 registers per lane) and of up to 1024 (128 per lane).
+// One workgroup per part (of the launch's list, if it has one).  A part whose
+// links fit keeps its link state in shared memory for the whole run; the
+// rest of the pool caches the path records of the flows being solved.  Built
+// for workgroups of up to 512 threads (256 registers per lane) and of up to
+// 1024 (128 per lane).
 template <int NT>
 __global__ __launch_bounds__(NT) void netsim_block_kernel(Params P) {
   __shared__ double lds[32];
@@ -2412,8 +2434,10 @@ __global__ __launch_bounds__(NT) void netsim_block_kernel(Params P) {
   __shared__ Tally tally;
   __shared__ Lists lists;
   __shared__ __align__(16) unsigned char pool[POOL_BYTES];
-  BlockG<(NT > 512)> g{lds, ldsi, &lists};
-  for (int sc = blockIdx.x; sc < P.num_scen; sc += gridDim.x) {
+  BlockG<false, (NT <= 512)> g{lds, ldsi, &lists};
+  const int parts = P.pcount ? *P.pcount : P.list ? P.num_list : P.num_scen;
+  for (int i = blockIdx.x; i < parts; i += gridDim.x) {
+    const int sc = P.list ? P.list[i] : i;
     const ScenCtl* C = &P.ctl[sc];
     if (threadIdx.x == 0) lists = Lists{};
     __syncthreads();
@@ -2449,7 +2473,7 @@ __global__ __launch_bounds__(NT) void netsim_solve_kernel(Params P) {
   __shared__ Tally tally;
   __shared__ Lists lists;
   __shared__ __align__(16) unsigned char pool[POOL_BYTES];
-  BlockG<(NT > 512)> g{lds, ldsi, &lists};
+  BlockG<false, false> g{lds, ldsi, &lists};
   for (int sc = blockIdx.x; sc < P.num_scen; sc += gridDim.x) {
     const ScenCtl* C = &P.ctl[sc];
     if (threadIdx.x == 0) lists = Lists{};
@@ -2559,7 +2583,7 @@ __global__ __launch_bounds__(1024) void netsim_cluster_kernel(Params P) {
     }
     return;
   }
-  BlockG<true> g{lds, ldsi, &lists};
+  BlockG<true, false> g{lds, ldsi, &lists};
   Assist as{P.bar, cw, nh, P.assist_min > 0 ? P.assist_min : 1, 0u, box};
   for (;;) {
     if (threadIdx.x == 0)

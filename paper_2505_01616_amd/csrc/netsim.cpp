@@ -70,6 +70,19 @@ struct netsim {
   std::vector<int32_t> h_pend0;
   std::vector<ScenCtl> h_ctl0;
   std::vector<int32_t> h_lfoff;       // exact mode: link-major incidence offsets
+  // block layout: the parts one wavefront runs, in classes by the shared
+  // memory they need, then those that start in the block kernel (positions
+  // in Params::list's array d_plist)
+  struct WaveClass {
+    int32_t first = 0, count = 0, sc = 0, pc = 0;
+    size_t lds = 0;
+    int32_t unsafe = 0;               // parts that may outgrow the lists
+  };
+  std::vector<WaveClass> wave;
+  int32_t big_first = 0, big_count = 0;
+  int32_t* d_plist = nullptr;
+  hipStream_t side = nullptr;         // block-kernel parts beside the wave kernel
+  hipEvent_t side_ev[2] = {};
   double scale = 1.0;
   void* d_block = nullptr;            // one allocation holding every device array
   void* d_hist = nullptr;             // rollback history (options.history_mb; exact mode: none)
@@ -278,6 +291,10 @@ constexpr int kExactThreads = 512;
 // enqueued this many at a time between looks at the unfrozen count.
 constexpr int32_t kExactGridMin = 16384;
 constexpr int kGridLevelBatch = 64;
+// Wave kernel: room for active and pending flows at most, and the classes of
+// parts by shared memory (32, 8 or fewer parts on a compute unit at once).
+constexpr int32_t kWaveSlots = 256, kWavePending = 512;
+constexpr size_t kWaveClassBytes[] = {5 * 1024, 20 * 1024, 150 * 1024};
 constexpr int DEBUG_EXACT_GRID = 32;  // options.debug bit 5: every such solve on the whole GPU
 
 netsim_status prepare(netsim_t* h) {
@@ -564,6 +581,53 @@ netsim_status prepare(netsim_t* h) {
     hist_bytes = (size_t)hb * sizeof(netsim_dev::HistUndo) + (size_t)eb * sizeof(netsim_dev::HistEv);
   }
   h->h_ctl0 = ctl;
+  // parts the wave kernel runs: path records, lists and link state that fit
+  // the shared memory, and no more flows released together at the start than
+  // the lists hold.  The others start in the block kernel.
+  std::vector<int32_t> plist;
+  h->wave.clear();
+  if (!exact) {
+    constexpr size_t kClasses = sizeof kWaveClassBytes / sizeof kWaveClassBytes[0];
+    std::vector<std::vector<int32_t>> in(kClasses);
+    std::vector<netsim::WaveClass> wc(kClasses);
+    std::vector<int32_t> big;
+    for (int32_t k = 0; k < NP; ++k) {
+      const ScenCtl& c = ctl[(size_t)k];
+      int32_t real = 0, roots = 0;
+      for (int32_t d = c.f0; d < c.f1; ++d) {
+        real += nbytes[(size_t)d] > 0.0;
+        roots += nbytes[(size_t)d] > 0.0 && ndeps[(size_t)d] == 0;
+      }
+      const int32_t sc = std::min(real, kWaveSlots), pc = std::min(c.f1 - c.f0, kWavePending);
+      const size_t z = netsim_dev::wave_bytes(c.l1 - c.l0, c.nc, sc, pc);
+      size_t q = 0;
+      while (q < kClasses && z > kWaveClassBytes[q]) ++q;
+      if (!c.lds_paths || roots > sc || c.n_pend0 > pc || q == kClasses) {
+        big.push_back(k);
+        continue;
+      }
+      in[q].push_back(k);
+      wc[q].sc = std::max(wc[q].sc, sc);
+      wc[q].pc = std::max(wc[q].pc, pc);
+      wc[q].unsafe += real > sc || c.f1 - c.f0 > pc;
+    }
+    for (size_t q = 0; q < kClasses; ++q) {
+      if (in[q].empty()) continue;
+      wc[q].first = (int32_t)plist.size();
+      wc[q].count = (int32_t)in[q].size();
+      // the class's lists are as long as its widest part's; what the links
+      // take is added per part
+      for (int32_t k : in[q])
+        wc[q].lds = std::max(wc[q].lds, netsim_dev::wave_bytes(ctl[(size_t)k].l1 - ctl[(size_t)k].l0,
+                                                               ctl[(size_t)k].nc, wc[q].sc, wc[q].pc));
+      plist.insert(plist.end(), in[q].begin(), in[q].end());
+      h->wave.push_back(wc[q]);
+    }
+    h->big_first = (int32_t)plist.size();
+    h->big_count = (int32_t)big.size();
+    plist.insert(plist.end(), big.begin(), big.end());
+  }
+  plist.resize((size_t)std::max<int32_t>(NP, 1), 0);
   // one device allocation, carved into aligned arrays
   const size_t Fz = (size_t)std::max<int64_t>(F, 1), Lz = (size_t)std::max<int64_t>(ld, 1);
   const size_t XL = h->opt.exact ? Lz : 1;
@@ -617,6 +681,8 @@ netsim_status prepare(netsim_t* h) {
       {(void**)&P.unf1, sizeof(int32_t) * Fz},
       {(void**)&P.bar, sizeof(uint32_t) * netsim_dev::BAR_WORDS},
       {(void**)&P.slots, sizeof(uint64_t) * 8},
+      {(void**)&h->d_plist, sizeof(int32_t) * plist.size()},
+      {(void**)&P.hlist, sizeof(int32_t) * plist.size()},
       // exact mode: link state in fp64 (one element each otherwise)
       {(void**)&P.capf, sizeof(double) * XL},
       {(void**)&P.xR, sizeof(double) * XL},
@@ -675,6 +741,7 @@ netsim_status prepare(netsim_t* h) {
       {path16.data(), P.path16, sizeof(uint16_t) * path16.size()},
       {lat.data(), P.lat, any_lat ? sizeof(double) * lat.size() : 0},
       {capf.data(), P.capf, h->opt.exact ? sizeof(double) * capf.size() : 0},
+      {plist.data(), h->d_plist, sizeof(int32_t) * plist.size()},
       {lfoff.data(), P.lfoff, sizeof(int32_t) * lfoff.size()},
       {lfid.data(), P.lfid, sizeof(int32_t) * lfid.size()},
       {lfchunk.data(), P.lfchunk, sizeof(int32_t) * lfchunk.size()},
@@ -686,6 +753,7 @@ netsim_status prepare(netsim_t* h) {
     if (he != hipSuccess) return hip_fail(h, he, "hipMemcpy (upload)");
   }
   if (!any_lat) P.lat = nullptr;  // no latency anywhere: arrival = last byte
+  P.hcount = reinterpret_cast<int32_t*>(P.bar + netsim_dev::BAR_HAND);
   P.num_scen = NP;
   P.scale = h->scale;
   P.inv_scale = 1.0 / h->scale;
@@ -728,6 +796,42 @@ netsim_status reset_state(netsim_t* h, hipStream_t st) {
   he = hipStreamSynchronize(st);
   if (he != hipSuccess) return hip_fail(h, he, "hipStreamSynchronize (reset)");
   return NETSIM_OK;
+}
+
+// The block layout's event loops: the small parts one wavefront each, the
+// others one workgroup each beside them (on a stream of the handle's own,
+// joined before the launch ends), then the parts the wave kernel handed over.
+hipError_t launch_event_loops(netsim_t* h, const Params& P0, int threads, hipStream_t st) {
+  Params P = P0;
+  hipError_t he = hipSuccess;
+  if (h->big_count > 0) {
+    if (!h->side) {
+      he = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
+      for (auto& ev : h->side_ev)
+        if (he == hipSuccess) he = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    }
+    if (he == hipSuccess) he = hipEventRecord(h->side_ev[0], st);
+    if (he == hipSuccess) he = hipStreamWaitEvent(h->side, h->side_ev[0], 0);
+    P.list = h->d_plist + h->big_first;
+    P.num_list = h->big_count;
+    if (he == hipSuccess) he = netsim_dev::launch_block(P, std::min<int32_t>(h->big_count, 1 << 20), threads, h->side);
+    if (he == hipSuccess) he = hipEventRecord(h->side_ev[1], h->side);
+  }
+  P.list = nullptr;
+  int32_t unsafe = 0;
+  for (const auto& w : h->wave) {
+    if (he == hipSuccess) he = netsim_dev::launch_wave(P, h->d_plist + w.first, w.count, w.sc, w.pc, w.lds, st);
+    unsafe += w.unsafe;
+  }
+  if (he == hipSuccess && unsafe > 0) {
+    P.list = P.hlist;
+    P.pcount = P.hcount;
+    P.hand = 1;
+    P.resume = 1;  // a part that has not started starts from t = 0
+    he = netsim_dev::launch_block(P, std::min<int32_t>(unsafe, 512), 512, st);
+  }
+  if (he == hipSuccess && h->big_count > 0) he = hipStreamWaitEvent(st, h->side_ev[1], 0);
+  return he;
 }
 
 // One kernel launch: a rate solve per part (solve_only), or the event loop of
@@ -835,8 +939,14 @@ netsim_status launch(netsim_t* h, hipStream_t st, bool solve_only, float* ms, bo
       int threads = h->opt.block_threads > 0 ? h->opt.block_threads : widest > 16384 ? 1024 : 512;
       threads = std::max(64, std::min(1024, threads / 64 * 64));
       const int blocks = std::max(1, std::min<int32_t>(S, 1 << 20));
-      he = solve_only ? netsim_dev::launch_solve(P, blocks, threads, st)
-                      : netsim_dev::launch_block(P, blocks, threads, st);
+      // a workgroup size asked for, and the device's consistency checks, are
+      // the block kernel's
+      if (solve_only)
+        he = netsim_dev::launch_solve(P, blocks, threads, st);
+      else if (!h->wave.empty() && h->opt.block_threads == 0 && (h->opt.debug & 1) == 0)
+        he = launch_event_loops(h, P, threads, st);
+      else
+        he = netsim_dev::launch_block(P, blocks, threads, st);
     }
   }
   if (he == hipSuccess) he = hipEventRecord(e1, st);
@@ -2212,6 +2322,9 @@ void netsim_destroy(netsim_t* h) {
   if (h->d_block) {
     (void)hipSetDevice(h->opt.device);
     drop_checkpoints(h);
+    for (hipEvent_t ev : h->side_ev)
+      if (ev) (void)hipEventDestroy(ev);
+    if (h->side) (void)hipStreamDestroy(h->side);
     (void)hipFree(h->d_block);
     if (h->d_hist) (void)hipFree(h->d_hist);
   }

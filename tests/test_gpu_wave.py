@@ -1,0 +1,103 @@
+"""GPU tests of the block layout's one-wave kernel against its workgroup
+kernel (block_threads asks for the latter): finish times and statistics bit
+for bit, at the edges of the wave kernel's lists (256 active and 512 pending
+flows, 64 finished flows at once), where a part is handed over in the middle
+of an event, and when the run is advanced in pieces across the hand-over."""
+
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import sim as osim
+from workloads.program import Barrier, PathFlow, Program, Scenario, Topology
+from workloads.rng import Stream
+
+pytestmark = pytest.mark.gpu
+
+SAME = ("events", "solves", "rounds", "flows_swept", "incidences_swept", "active_swept", "pending_swept",
+        "reselected", "completed_flows", "links_swept", "launch_events")
+
+
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2505_01616_amd import netsim as ns
+    from paper_2505_01616_amd import program as prog
+    return ns, prog
+
+
+def _say(*a):
+    print(*a, file=sys.stderr, flush=True)
+
+
+def _release(n, lagged, latency=False, links=40, seed=9):
+    """A flow, then n flows released by its end (all at once, or each at an
+    instant of its own), then a barrier over them and 150 zero-byte flows
+    that finish together, each with a flow after it."""
+    u = Stream(seed, "wave-release").u01(8 * n + 1000)
+    caps = 1.0 + np.floor(9.0 * u[:links])
+    topo = Topology(kind="explicit", capacities=caps)
+    if latency:
+        topo.latencies = 0.25 * u[links:2 * links]
+    sc = Scenario(topo)
+    first = sc.add(PathFlow([0], 8.0))
+    ids = []
+    for i in range(n):
+        r = u[100 + 8 * i:108 + 8 * i]
+        path = sorted({int(x * links) for x in r[:1 + int(6 * r[6])]})
+        ids.append(sc.add(PathFlow(path, float(1 + int(40 * r[7])), lag=float(1.0 + 7.0 * r[5]) if lagged else 0.0,
+                                   after=(first,))))
+    b = sc.add(Barrier(after=tuple(ids)))
+    for i in range(150):
+        z = sc.add(Barrier(after=(b,)))
+        sc.add(PathFlow([i % links], 2.0 + i % 7, after=(z,)))
+    return Program(f"release-{n}", [sc])
+
+
+@pytest.mark.parametrize("latency", [False, True])
+@pytest.mark.parametrize("n,lagged", [(255, False), (256, False), (257, False), (700, False), (511, True),
+                                      (512, True), (513, True), (1500, True)])
+def test_hand_over(n, lagged, latency):
+    ns, pr = _gpu()
+    program = _release(n, lagged, latency)
+    _say(f"test_hand_over n={n} lagged={lagged} latency={latency}")
+    a, sa = pr.run_program(program, ns.make_options())
+    b, sb = pr.run_program(program, ns.make_options(block_threads=512))
+    assert np.array_equal(a[0], b[0])
+    for k in SAME:
+        assert sa[k] == sb[k], (k, sa[k], sb[k])
+    want = osim.run_scenario(program.scenarios[0]).finish
+    assert np.max(np.abs(a[0] - want) / want) < 1e-9
+
+
+@pytest.mark.parametrize("history", [0, 8])
+@pytest.mark.parametrize("n,lagged", [(40, False), (300, False), (600, True)])
+def test_pieces_and_rollback(n, lagged, history):
+    """Advancing by events (the launch's limit counts both kernels' events)
+    equals one run, before and after a start moves into the past."""
+    ns, pr = _gpu()
+    program = _release(n, lagged)
+    _say(f"test_pieces_and_rollback n={n} lagged={lagged} history={history}")
+    want, _ = pr.run_program(program, ns.make_options(block_threads=512))
+    later = _release(n, lagged)
+    op = later.scenarios[0].ops[20]
+    op.lag = op.lag + 3.5
+    want2, _ = pr.run_program(later, ns.make_options(block_threads=512))
+    ld = pr.load_program(program, ns.make_options(history_mb=history))
+    try:
+        events = 0
+        for _ in range(2000):
+            ns.netsim_advance(ld.handle, max_events=7)
+            st = ns.netsim_get_stats(ld.handle)
+            assert st["launch_events"] <= 7 and st["events"] == events + st["launch_events"]
+            events = st["events"]
+            if st["complete"]:
+                break
+        assert np.array_equal(ns.netsim_get_finish(ld.handle), want[0])
+        ns.netsim_update_start(ld.handle, 20, op.lag)
+        ns.netsim_advance(ld.handle)
+        assert np.array_equal(ns.netsim_get_finish(ld.handle), want2[0])
+    finally:
+        ld.close()
