@@ -586,7 +586,7 @@ netsim_status netsim_bench_sweeps(netsim_t* h, int32_t scen, int64_t n_active,
  * hip_stream (NULL: the default stream); it never synchronises, so the
  * caller reads d_status and d_rates after the stream has reached that
  * point.  Limits: num_links <= 65536, num_flows <= 262144 (NETSIM_E_LIMIT
- * beyond).  Working memory is one static device array of about 5 MB per
+ * beyond).  Working memory is one static device array of about 18 MB per
  * device, held until the process ends and found once per device; nothing
  * is allocated or freed by the call.  Calls that overlap on one device
  * (different host threads, or different streams of one device) share that

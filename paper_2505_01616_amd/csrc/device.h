@@ -193,6 +193,7 @@ struct Params {
   double* xs;              // [L] fair share of the current level
   int32_t* xn;             // [L] unfrozen flows
   int32_t* xk;             // [L] flows frozen at the current level
+  void* xpair;             // [L] 16 bytes: residual and count of a solve by links (filling.h)
   int32_t* xlive0; int32_t* xlive1;  // [L] links with unfrozen flows (per part on [l0, l1))
   // link-major incidence (exact mode): the flows of device link l are
   // lfid[lfoff[l] .. lfoff[l+1]-1] (ascending); lfchunk[c] is the link of
@@ -264,6 +265,11 @@ hipError_t grid_solve_count(const Params& P, const ScenCtl& C, int e0, int e1, h
 hipError_t grid_solve_links(const Params& P, const ScenCtl& C, int j, hipStream_t s);
 hipError_t grid_solve_freeze(const Params& P, const ScenCtl& C, int n, int j, hipStream_t s,
                              unsigned long long* stamps = nullptr);
+// Every level of the solve after begin and count, by one workgroup
+// (filling.h), where the part's links fit its lists; sets xgrid->levels, fsw,
+// done or fault, isw[0] and lsw[0].
+bool grid_solve_fill_fits(const ScenCtl& C);
+hipError_t grid_solve_fill(const Params& P, const ScenCtl& C, int n, int max_rounds, hipStream_t s);
 // Workgroups of the count and freezing sweeps.  With `stamps` (device,
 // 2 x workgroups words) each workgroup's first thread writes the wall clock
 // (100 MHz) at its start and end: the sweep's duration inside the kernel.

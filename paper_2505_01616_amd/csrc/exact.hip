@@ -32,6 +32,7 @@
 // integer counts.  Nothing depends on the order in which threads run, so the
 // finish times are the same bit for bit for any workgroup size.
 #include "device.h"
+#include "filling.h"
 #include "netsim.h"
 
 #include <math.h>
@@ -561,95 +562,308 @@ int exact_link_bytes() { return XLINK_BYTES; }
 
 // ------------------------------------------- allocation-free rate solve
 // Scratch of netsim_solve_rates_noalloc: per link R, s (f64), n, k and two
-// live lists (i32); per flow the solve list and two unfrozen lists (i32);
-// a status block.  The array lives in device memory for the whole process
-// (one copy per device); host code reaches it only through the address
-// hipGetSymbolAddress returns for the current device.
+// live lists, a number among the links in use and where its flows start
+// (i32), share and rest as filling.h keeps them (16 bytes each); per flow the solve list and two unfrozen lists (i32); the flows of
+// every link and the paths in numbers of links in use (i32 per incidence).
+// The array lives in device memory for the whole process (one copy per
+// device); host code reaches it only through the address hipGetSymbolAddress
+// returns for the current device.
 constexpr int NA_MAX_LINKS = 1 << 16;
 constexpr int NA_MAX_FLOWS = 1 << 18;
-constexpr size_t NA_LINK_BYTES = (size_t)NA_MAX_LINKS * (8 + 8 + 4 + 4 + 4 + 4);
+constexpr int NA_MAX_PAIRS = 6 * NA_MAX_FLOWS;  // incidences the link-major form holds
+constexpr size_t NA_LINK_BYTES = (size_t)NA_MAX_LINKS * (8 + 8 + 4 + 4 + 4 + 4 + 4 + 4 + 16 + 16);
 constexpr size_t NA_FLOW_BYTES = (size_t)NA_MAX_FLOWS * (4 + 4 + 4);
+constexpr size_t NA_PAIR_BYTES = (size_t)NA_MAX_PAIRS * 4 + (size_t)NA_MAX_FLOWS * 16;
 constexpr size_t NA_HEAD_BYTES = 256;  // kept free (alignment of what follows)
 constexpr int ST_BAD_INPUT = -100;
-constexpr size_t NA_SCRATCH_BYTES = NA_HEAD_BYTES + NA_LINK_BYTES + NA_FLOW_BYTES;
+constexpr size_t NA_SCRATCH_BYTES = NA_HEAD_BYTES + NA_LINK_BYTES + NA_FLOW_BYTES + NA_PAIR_BYTES + 256;
+// Flows from which the solve goes by links (filling.h): below, a sweep over
+// all flows is one step per thread and the link-major form (30 to 50 us to
+// make) does not pay.  At 1,200 to 5,000 flows the two are within 25% of each
+// other either way (fewer levels: sweeps), from 10,000 the links win by 2 to 8.
+constexpr int NA_INDEX_MIN = 1024;
+constexpr size_t NA_LDS_LINK_BYTES = 48 * 1024;  // link state of a small solve in shared memory
 
-// One workgroup: validates the caller's CSR (offsets from 0, non-decreasing;
-// every path non-empty, its link ids in range and distinct; capacities
-// finite and > 0), then runs the exact solve over all F flows with link
-// state in the scratch array.
+struct NaScratch {
+  FillShare* a;
+  FillRest* b;
+  double *R, *S;
+  int32_t *n, *k, *live0, *live1, *num, *off, *U, *unf0, *unf1, *lf;
+  uint4* rec;
+  __device__ __forceinline__ explicit NaScratch(unsigned char* ws) {
+    a = reinterpret_cast<FillShare*>(ws + NA_HEAD_BYTES);
+    b = reinterpret_cast<FillRest*>(a + NA_MAX_LINKS);
+    rec = reinterpret_cast<uint4*>(b + NA_MAX_LINKS);
+    R = reinterpret_cast<double*>(rec + NA_MAX_FLOWS);
+    S = R + NA_MAX_LINKS;
+    n = reinterpret_cast<int32_t*>(S + NA_MAX_LINKS);
+    k = n + NA_MAX_LINKS;
+    live0 = k + NA_MAX_LINKS;
+    live1 = live0 + NA_MAX_LINKS;
+    num = live1 + NA_MAX_LINKS;
+    U = num + NA_MAX_LINKS;
+    unf0 = U + NA_MAX_FLOWS;
+    unf1 = unf0 + NA_MAX_FLOWS;
+    lf = unf1 + NA_MAX_FLOWS;
+    off = lf + NA_MAX_PAIRS;  // [NA_MAX_LINKS + 1]
+  }
+};
+
+// Checks the caller's CSR (offsets from 0, non-decreasing; every path
+// non-empty, its link ids in range and distinct; capacities finite and > 0):
+// *bad = INT32_MAX, or the first flow, or F + the first link, that fails.
+// Followed by a workgroup barrier.
+__device__ __forceinline__ void na_check(const double* cap, int L, const int32_t* poff, const int32_t* plink, int F,
+                                         int32_t* U, int* bad) {
+  const int T = blockDim.x, tid = threadIdx.x;
+  if (tid == 0) *bad = INT32_MAX;
+  __syncthreads();
+  if (tid == 0 && F > 0 && poff[0] != 0) atomicMin(bad, 0);
+  for (int f = tid; f < F; f += T) {
+    const int e0 = poff[f], e1 = poff[f + 1];
+    bool ok = e1 > e0;
+    // the first six links at once, compared in registers
+    int lv[6];
+#pragma unroll
+    for (int q = 0; q < 6; ++q) lv[q] = e0 + q < e1 ? plink[e0 + q] : -2 - q;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+      if (e0 + q < e1) ok = ok && lv[q] >= 0 && lv[q] < L;
+#pragma unroll
+      for (int r = 0; r < q; ++r) ok = ok && lv[r] != lv[q];
+    }
+    for (int e = e0 + 6; ok && e < e1; ++e) {
+      const int l = plink[e];
+      ok = l >= 0 && l < L;
+      for (int q = e0; ok && q < e; ++q) ok = plink[q] != l;
+    }
+    if (!ok) atomicMin(bad, f);
+    U[f] = f;
+  }
+  for (int l = tid; l < L; l += T) {
+    const double c = cap[l];
+    if (!(c > 0.0) || !(c < XINF)) atomicMin(bad, F + l);
+  }
+  __syncthreads();
+}
+
+// The solve by sweeps over all flows (exact_solve): lists in the scratch
+// array, link state there or (LDS) in the given shared memory.
+template <bool LDS>
+__device__ __forceinline__ int na_sweeps(const double* cap, int L, const int32_t* poff, const int32_t* plink, int F,
+                                         double* rates, const NaScratch& w, int max_rounds, XShared& sh,
+                                         int64_t& levels, unsigned char* pool = nullptr) {
+  Params P{};
+  P.poff = poff;
+  P.plink = plink;
+  P.capf = cap;
+  P.rate = rates;
+  P.xR = w.R;
+  P.xs = w.S;
+  P.xn = w.n;
+  P.xk = w.k;
+  P.xlive0 = w.live0;
+  P.xlive1 = w.live1;
+  P.unf0 = w.unf0;
+  P.unf1 = w.unf1;
+  P.max_rounds = max_rounds;
+  ScenCtl C{};
+  C.f0 = 0;
+  C.f1 = F;
+  C.l0 = 0;
+  C.l1 = L;
+  XLinks<LDS> lk;
+  if constexpr (LDS) {
+    lk = xlinks<true>(P, &C, pool);
+  } else {
+    lk = XLinks<false>{w.R, w.S, w.n, w.k, 0};
+  }
+  if (threadIdx.x == 0) {
+    sh.fsw = 0;
+    sh.isw = 0;
+    sh.lsw = 0;
+  }
+  __syncthreads();
+  int rb = 0;
+  return F > 0 ? exact_solve<LDS>(P, &C, lk, sh, rb, w.U, F, levels) : ST_DONE;
+}
+
+// The C status codes of include/netsim.h.
+__device__ __forceinline__ void na_report(int status, int bad, int64_t levels, int64_t* status_out) {
+  status_out[0] = status == ST_DONE ? 0 : status == ST_BAD_INPUT ? -1 : status == ST_ROUNDS ? -5 : -3;
+  status_out[1] = status == ST_BAD_INPUT ? (int64_t)bad : levels;
+}
+
+// One workgroup: checks the input, then runs the exact solve over all F
+// flows.  Such a small solve is bound by its dozen dependent steps, so link
+// state goes to shared memory where it fits (LDS) and a few hundred flows take
+// 256 threads: 240 flows over 249 links SMALL_US.
+template <bool LDS>
 __global__ __launch_bounds__(1024) void netsim_noalloc_solve_kernel(const double* cap, int L,
                                                                     const int32_t* poff,
                                                                     const int32_t* plink, int F,
                                                                     double* rates, int64_t* status_out,
                                                                     unsigned char* ws, int max_rounds) {
+  extern __shared__ __align__(16) unsigned char spool[];
   __shared__ XShared sh;
   __shared__ int bad;
-  double* R = reinterpret_cast<double*>(ws + NA_HEAD_BYTES);
-  double* S = R + NA_MAX_LINKS;
-  int32_t* n = reinterpret_cast<int32_t*>(S + NA_MAX_LINKS);
-  int32_t* k = n + NA_MAX_LINKS;
-  int32_t* live0 = k + NA_MAX_LINKS;
-  int32_t* live1 = live0 + NA_MAX_LINKS;
-  int32_t* U = live1 + NA_MAX_LINKS;
-  int32_t* unf0 = U + NA_MAX_FLOWS;
-  int32_t* unf1 = unf0 + NA_MAX_FLOWS;
-  const int T = blockDim.x, tid = threadIdx.x;
-  if (tid == 0) bad = INT32_MAX;
-  __syncthreads();
-  if (tid == 0 && F > 0 && poff[0] != 0) atomicMin(&bad, 0);
-  for (int f = tid; f < F; f += T) {
-    const int e0 = poff[f], e1 = poff[f + 1];
-    bool ok = e1 > e0;
-    for (int e = e0; ok && e < e1; ++e) {
-      const int l = plink[e];
-      ok = l >= 0 && l < L;
-      for (int q = e0; ok && q < e; ++q) ok = plink[q] != l;
-    }
-    if (!ok) atomicMin(&bad, f);
-    U[f] = f;
-  }
-  for (int l = tid; l < L; l += T) {
-    const double c = cap[l];
-    if (!(c > 0.0) || !(c < XINF)) atomicMin(&bad, F + l);
-  }
-  __syncthreads();
+  const NaScratch w(ws);
+  na_check(cap, L, poff, plink, F, w.U, &bad);
   int status = ST_BAD_INPUT;
   int64_t levels = 0;
-  if (bad == INT32_MAX) {
-    Params P{};
-    P.poff = poff;
-    P.plink = plink;
-    P.capf = cap;
-    P.rate = rates;
-    P.xR = R;
-    P.xs = S;
-    P.xn = n;
-    P.xk = k;
-    P.xlive0 = live0;
-    P.xlive1 = live1;
-    P.unf0 = unf0;
-    P.unf1 = unf1;
-    P.max_rounds = max_rounds;
-    ScenCtl C{};
-    C.f0 = 0;
-    C.f1 = F;
-    C.l0 = 0;
-    C.l1 = L;
-    XLinks<false> lk{R, S, n, k, 0};
-    if (tid == 0) {
-      sh.fsw = 0;
-      sh.isw = 0;
-      sh.lsw = 0;
-    }
+  if (bad == INT32_MAX) status = na_sweeps<LDS>(cap, L, poff, plink, F, rates, w, max_rounds, sh, levels, spool);
+  if (threadIdx.x == 0) na_report(status, bad, levels, status_out);
+}
+
+// A flow's links as numbers of links in use: the first six in its record (16
+// bits each) beside their number, the others looked up.
+struct NaPaths {
+  const uint4* rec;
+  const int32_t *poff, *plink, *num;
+  __device__ __forceinline__ void load(int f, int* lv, int& deg) const {
+    const uint4 r = rec[f];
+    const uint32_t w[3] = {r.x, r.y, r.z};
+    deg = (int)r.w;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) lv[q] = (int)((w[q >> 1] >> (16 * (q & 1))) & 0xFFFFu);
+  }
+  __device__ __forceinline__ int more(int f, int j) const { return num[plink[poff[f] + j]]; }
+};
+
+// The same solve for many flows: the links in use are numbered and the
+// flows of each listed (a count, a prefix sum over the links, a fill), then
+// the levels go by links (filling.h) with link state in shared memory where it
+// fits.  32,256 flows over 2,560 links (1,461 levels): a sweep over the
+// unfrozen flows at every level takes 39 us a level, bound by the gathers of
+// all their links; this 5 us.  More links or incidences than the lists hold take the
+// sweeps as before.
+__global__ __launch_bounds__(1024) void netsim_noalloc_index_kernel(const double* cap, int L, const int32_t* poff,
+                                                                    const int32_t* plink, int F, double* rates,
+                                                                    int64_t* status_out, unsigned char* ws,
+                                                                    int max_rounds) {
+  extern __shared__ __align__(16) unsigned char npool[];
+  __shared__ FillShared fs;
+  __shared__ XShared sh;
+  __shared__ int bad;
+  __shared__ uint64_t wtot[17];
+  const NaScratch w(ws);
+  const int T = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  na_check(cap, L, poff, plink, F, w.U, &bad);
+  if (bad != INT32_MAX) {
+    if (tid == 0) na_report(ST_BAD_INPUT, bad, 0, status_out);
+    return;
+  }
+  const int pairs = poff[F];
+  int status = ST_DONE;
+  int64_t levels = 0;
+  bool by_links = pairs <= NA_MAX_PAIRS;
+  int nl = 0;
+  if (by_links) {
+    for (int l = tid; l < L; l += T) w.n[l] = 0;
     __syncthreads();
-    int rb = 0;
-    status = F > 0 ? exact_solve<false>(P, &C, lk, sh, rb, U, F, levels) : ST_DONE;
+    for (int e = tid; e < pairs; e += T)
+      __hip_atomic_fetch_add(&w.n[plink[e]], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+    // numbers of the links in use and where their flows start: prefix sums
+    // (links in use in the upper half of a word, incidences in the lower)
+    uint64_t base = 0;
+    for (int l0 = 0; l0 < L; l0 += T) {
+      const int l = l0 + tid;
+      const int c = l < L ? __hip_atomic_load(&w.n[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0;
+      const uint64_t own = c > 0 ? (1ull << 32) | (uint64_t)c : 0ull;
+      uint64_t v = own;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t u = __shfl_up(v, o, 64);
+        if (lane >= o) v += u;
+      }
+      if (lane == 63) wtot[wave] = v;
+      __syncthreads();
+      uint64_t before = base, all = base;
+      for (int j = 0; j < (T >> 6); ++j) {
+        if (j < wave) before += wtot[j];
+        all += wtot[j];
+      }
+      before += v - own;
+      if (l < L) {
+        w.num[l] = c > 0 ? (int32_t)(before >> 32) : -1;
+        if (c > 0) {
+          const int d = (int)(before >> 32);
+          w.off[d] = (int32_t)(before & 0xFFFFFFFFu);
+          w.k[d] = (int32_t)(before & 0xFFFFFFFFu);  // where the link's next flow goes
+          w.live0[d] = l;
+        }
+      }
+      base = all;
+      __syncthreads();
+    }
+    nl = (int)(base >> 32);
+    if (tid == 0) w.off[nl] = pairs;
+    by_links = fill_bytes(nl, F, false) <= FILL_DYNAMIC;
   }
-  if (tid == 0) {
-    // the C status codes of include/netsim.h
-    status_out[0] = status == ST_DONE ? 0 : status == ST_BAD_INPUT ? -1 : status == ST_ROUNDS ? -5 : -3;
-    status_out[1] = status == ST_BAD_INPUT ? (int64_t)bad : levels;
+  if (by_links) {
+    __syncthreads();
+    for (int f = tid; f < F; f += T) {
+      const int e0 = poff[f], e1 = poff[f + 1];
+      uint4 rec = make_uint4(0u, 0u, 0u, (uint32_t)(e1 - e0));
+      for (int e = e0; e < e1; e += 6) {  // six at a time, their steps in flight together
+        int d[6], at[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) d[q] = e + q < e1 ? plink[e + q] : -1;
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+          if (d[q] >= 0) d[q] = w.num[d[q]];
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+          if (d[q] >= 0) at[q] = __hip_atomic_fetch_add(&w.k[d[q]], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+          if (d[q] >= 0) w.lf[at[q]] = f;
+        if (e == e0) {
+#pragma unroll
+          for (int q = 0; q < 6; ++q) d[q] = d[q] < 0 ? 0 : d[q];
+          rec.x = (uint32_t)d[0] | (uint32_t)d[1] << 16;
+          rec.y = (uint32_t)d[2] | (uint32_t)d[3] << 16;
+          rec.z = (uint32_t)d[4] | (uint32_t)d[5] << 16;
+        }
+      }
+      w.rec[f] = rec;
+    }
+    const bool in_lds = fill_bytes(nl, F, true) <= FILL_DYNAMIC;
+    const size_t lpad = ((size_t)nl + 7) & ~size_t(7);
+    unsigned char* p = npool + fill_bytes(nl, 0, false);
+    const NaPaths paths{w.rec, poff, plink, w.num};
+    FillStats st;
+    auto levels_of = [&](const auto lk, uint32_t* bits) {
+      for (int q = tid; q < (F + 31) / 32; q += T) bits[q] = ~0u;
+      __syncthreads();
+      if (tid >= FILL_THREADS) return (int)ST_DONE;  // the levels take fewer threads than the lists
+      auto take = [&](int f) {
+        const uint32_t b = 1u << (f & 31);
+        return (atomicAnd(&bits[f >> 5], ~b) & b) != 0;
+      };
+      auto link = [&](int d, double& R, int& c) {
+        R = cap[w.live0[d]];
+        c = w.off[d + 1] - w.off[d];
+      };
+      return fill_levels(fs, lk, npool, nl, link, w.lf, F, rates, w.unf0, w.unf1, max_rounds, take, paths, st);
+    };
+    if (in_lds) {
+      FillShLinks lk;
+      lk.R = reinterpret_cast<double*>(p);
+      lk.s = lk.R + lpad;
+      lk.n = reinterpret_cast<int32_t*>(lk.s + lpad);
+      lk.off = w.off;
+      status = levels_of(lk, reinterpret_cast<uint32_t*>(p + 20 * lpad));
+    } else {
+      status = levels_of(FillGlLinks{w.a, w.b, w.off}, reinterpret_cast<uint32_t*>(p));
+    }
+    levels = st.levels;
+  } else {
+    __syncthreads();
+    status = na_sweeps<false>(cap, L, poff, plink, F, rates, w, max_rounds, sh, levels);
   }
+  if (tid == 0) na_report(status, bad, levels, status_out);
 }
 
 // The scratch array's device address on each device, found once per device.
@@ -699,13 +913,28 @@ extern "C" netsim_status netsim_solve_rates_noalloc(int32_t device, int32_t num_
       he = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
       if (he != hipSuccess || !p)
         return fail(NETSIM_E_DEVICE, std::string("hipGetSymbolAddress: ") + hipGetErrorString(he));
+      he = hipFuncSetAttribute((const void*)netsim_noalloc_index_kernel,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)FILL_DYNAMIC);
+      if (he != hipSuccess)
+        return fail(NETSIM_E_DEVICE, std::string("hipFuncSetAttribute: ") + hipGetErrorString(he));
       g_scratch_ptr[device] = static_cast<unsigned char*>(p);
     }
     ws = g_scratch_ptr[device];
   }
-  hipLaunchKernelGGL(netsim_noalloc_solve_kernel, dim3(1), dim3(1024), 0,
-                     static_cast<hipStream_t>(hip_stream), d_capacity_Bps, num_links, d_path_off,
-                     d_path_link, num_flows, d_rates, d_status, ws, num_flows + 1);
+  const int threads = num_flows <= 512 && num_links <= 1024 ? 256 : 1024;
+  const size_t links = (size_t)num_links * XLINK_BYTES;
+  if (num_flows < NA_INDEX_MIN && links <= NA_LDS_LINK_BYTES)
+    hipLaunchKernelGGL(netsim_noalloc_solve_kernel<true>, dim3(1), dim3(threads), links,
+                       static_cast<hipStream_t>(hip_stream), d_capacity_Bps, num_links, d_path_off,
+                       d_path_link, num_flows, d_rates, d_status, ws, num_flows + 1);
+  else if (num_flows < NA_INDEX_MIN)
+    hipLaunchKernelGGL(netsim_noalloc_solve_kernel<false>, dim3(1), dim3(1024), 0,
+                       static_cast<hipStream_t>(hip_stream), d_capacity_Bps, num_links, d_path_off,
+                       d_path_link, num_flows, d_rates, d_status, ws, num_flows + 1);
+  else
+    hipLaunchKernelGGL(netsim_noalloc_index_kernel, dim3(1), dim3(1024), FILL_DYNAMIC,
+                       static_cast<hipStream_t>(hip_stream), d_capacity_Bps, num_links, d_path_off,
+                       d_path_link, num_flows, d_rates, d_status, ws, num_flows + 1);
   he = hipGetLastError();
   if (he != hipSuccess) return fail(NETSIM_E_DEVICE, std::string("solve_rates_noalloc: ") + hipGetErrorString(he));
   return NETSIM_OK;

@@ -290,6 +290,7 @@ constexpr int kExactThreads = 512;
 // runs on the whole GPU (sweep.hip) instead of one workgroup; levels are
 // enqueued this many at a time between looks at the unfrozen count.
 constexpr int32_t kExactGridMin = 16384;
+constexpr int32_t kExactFillMin = 1024;
 constexpr int kGridLevelBatch = 64;
 // Wave kernel: room for active and pending flows at most, and the classes of
 // parts by shared memory (32, 8 or fewer parts on a compute unit at once).
@@ -689,6 +690,7 @@ netsim_status prepare(netsim_t* h) {
       {(void**)&P.xs, sizeof(double) * XL},
       {(void**)&P.xn, sizeof(int32_t) * XL},
       {(void**)&P.xk, sizeof(int32_t) * XL},
+      {(void**)&P.xpair, 16 * XL},
       {(void**)&P.xlive0, sizeof(int32_t) * XL},
       {(void**)&P.xlive1, sizeof(int32_t) * XL},
       {(void**)&P.lfoff, sizeof(int32_t) * (XL + 1)},
@@ -1070,9 +1072,11 @@ netsim_status simulate(netsim_t* h, hipStream_t st, bool resume, int64_t max_eve
 }
 
 
-// A wide exact solve of the n flows of part p listed in its act0 slice, on
-// the whole GPU (sweep.hip).  Levels are enqueued in batches; the host reads
-// the unfrozen count after each batch.  Adds the solve's statistics to *out.
+// A wide exact solve of the n flows of part p listed in its act0 slice
+// (sweep.hip): counts on the whole GPU, then every level by one workgroup
+// that looks only at what a level changes; or (more links than its lists
+// hold, or debug bit 5) each level on the whole GPU, enqueued in batches, the
+// host reading the unfrozen count after each batch.  Adds the solve's statistics to *out.
 struct GridStats {
   unsigned long long levels = 0, fsw = 0, isw = 0, lsw = 0;
 };
@@ -1085,6 +1089,22 @@ netsim_status grid_solve(netsim_t* h, hipStream_t st, int32_t p, int32_t n, Grid
     he = netsim_dev::grid_solve_count(P, C, h->h_lfoff[(size_t)C.l0], h->h_lfoff[(size_t)C.l1], st);
   const int64_t limit = h->opt.max_rounds > 0 ? h->opt.max_rounds : (int64_t)n + 1;
   netsim_dev::XGridHead g{};  // the counters the host reads
+  if (netsim_dev::grid_solve_fill_fits(C) && (h->opt.debug & DEBUG_EXACT_GRID) == 0) {
+    if (he == hipSuccess) he = netsim_dev::grid_solve_fill(P, C, n, (int)std::min<int64_t>(limit, INT32_MAX), st);
+    unsigned long long isw = 0, lsw = 0;
+    if (he == hipSuccess) he = hipMemcpyAsync(&g, P.xgrid, sizeof g, hipMemcpyDeviceToHost, st);
+    if (he == hipSuccess) he = hipMemcpyAsync(&isw, P.xgrid->isw, sizeof isw, hipMemcpyDeviceToHost, st);
+    if (he == hipSuccess) he = hipMemcpyAsync(&lsw, P.xgrid->lsw, sizeof lsw, hipMemcpyDeviceToHost, st);
+    if (he == hipSuccess) he = hipStreamSynchronize(st);
+    if (he != hipSuccess) return hip_fail(h, he, "wide exact solve");
+    if (g.fault) return fail(h, NETSIM_E_DEVICE, "device solver fault: non-positive fair share");
+    if (!g.done) return fail(h, NETSIM_E_LIMIT, "device solver fault: round watchdog fired");
+    out->levels += g.levels;
+    out->fsw += g.fsw;
+    out->isw += isw;
+    out->lsw += lsw;
+    return NETSIM_OK;
+  }
   // levels 0 and 1 directly; then batches of kGridLevelBatch levels replayed
   // from one captured graph (the kernels use only the parity of the level
   // and whether it is the first, so the batch captured as levels 2, 3, ...
@@ -2141,7 +2161,8 @@ netsim_status netsim_solve_once(netsim_t* h, int32_t scen, int64_t n_active, con
   if (h->opt.exact)
     for (int32_t k = 0; k < h->num_parts; ++k) {
       ScenCtl& c = ctl[(size_t)k];
-      if (c.n_solve > 0 && (c.n_solve >= kExactGridMin || (h->opt.debug & DEBUG_EXACT_GRID))) {
+      if (c.n_solve > 0 && (c.n_solve >= kExactGridMin || (h->opt.debug & DEBUG_EXACT_GRID) ||
+                            (c.n_solve >= kExactFillMin && netsim_dev::grid_solve_fill_fits(c)))) {
         wide.emplace_back(k, c.n_solve);
         c.n_solve = 0;
       }

@@ -29,10 +29,12 @@
 // (the other parity's counters are stale by then), which lets the host
 // enqueue levels in batches.
 #include "device.h"
+#include "filling.h"
 
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #pragma clang fp contract(off)
 
@@ -448,6 +450,95 @@ __global__ __launch_bounds__(256) void exact_freeze_kernel(Params P, int l0, int
   }
 }
 
+// ------------------------------------------------ levels by one workgroup
+// A flow's links from its path record (six part-local ids at most) or the
+// path CSR.
+template <bool REC>
+struct FillPaths {
+  const uint4* rec;
+  const int32_t* poff;
+  const int32_t* plink;
+  int l0;
+  __device__ __forceinline__ void load(int f, int* lv, int& deg) const {
+    if constexpr (REC) {
+      const uint4 r = rec[f];
+      const uint32_t w[3] = {r.x, r.y, r.z};
+      deg = 0;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        const uint32_t u = (w[q >> 1] >> (16 * (q & 1))) & 0xFFFFu;
+        lv[q] = (int)u;
+        deg += u != 0xFFFFu;
+      }
+    } else {
+      const int e0 = poff[f];
+      deg = poff[f + 1] - e0;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) lv[q] = q < deg ? plink[e0 + q] - l0 : 0;
+    }
+  }
+  __device__ __forceinline__ int more(int f, int j) const {
+    if constexpr (REC) return 0;
+    else return plink[poff[f] + j] - l0;
+  }
+};
+
+// All levels of a solve (filling.h) after the count, in place of the
+// kernels above: 258,048 flows over 20,480 links (11,744 levels) with link
+// state in global memory, or any solve whose links fit shared memory (LDSL).
+// BITS: the flows' bits are kept in shared memory as well.
+template <bool REC, bool BITS, bool LDSL>
+__global__ __launch_bounds__(FILL_THREADS) void exact_fill_kernel(Params P, int l0, int l1, int f0, int f1, int n,
+                                                                  int max_rounds, XGrid* g) {
+  extern __shared__ __align__(16) unsigned char fpool[];
+  __shared__ FillShared sh;
+  const int nl = l1 - l0, tid = threadIdx.x;
+  const size_t lpad = ((size_t)nl + 7) & ~size_t(7);
+  unsigned char* p = fpool + fill_bytes(nl, 0, false);
+  using Links = std::conditional_t<LDSL, FillShLinks, FillGlLinks>;
+  Links lk;
+  lk.off = P.lfoff + l0;
+  if constexpr (LDSL) {
+    lk.R = reinterpret_cast<double*>(p);
+    lk.s = lk.R + lpad;
+    lk.n = reinterpret_cast<int32_t*>(lk.s + lpad);
+    p += 20 * lpad;
+  } else {
+    // arrays of the default solver, which exact mode does not run
+    lk.a = reinterpret_cast<FillShare*>(P.lst) + l0;
+    lk.b = reinterpret_cast<FillRest*>(P.xpair) + l0;
+  }
+  const int w0 = f0 >> 5;
+  uint32_t* bits = reinterpret_cast<uint32_t*>(p);
+  if constexpr (BITS)
+    if (f1 > f0)
+      for (int w = w0 + tid; w <= ((f1 - 1) >> 5); w += blockDim.x) bits[w - w0] = P.xmask[w];
+  __syncthreads();
+  auto take = [&](int f) {
+    const uint32_t b = 1u << (f & 31);
+    if constexpr (BITS) return (atomicAnd(&bits[(f >> 5) - w0], ~b) & b) != 0;
+    else return (atomicAnd(&P.xmask[f >> 5], ~b) & b) != 0;
+  };
+  const FillPaths<REC> paths{P.path16, P.poff, P.plink, l0};
+  FillStats st;
+  auto link = [&](int l, double& R, int& c) {
+    R = P.capf[l0 + l];
+    c = P.xn[l0 + l];
+  };
+  const int rc = fill_levels(sh, lk, fpool, nl, link, P.lfid, n, P.rate, P.xlive0 + l0, P.xlive1 + l0, max_rounds,
+                             take, paths, st);
+  if (tid == 0) {
+    g->fault = rc == ST_BAD_SHARE;
+    g->done = rc == ST_DONE;
+    g->ublocks = 1;
+    g->lblocks = 1;
+    g->levels = (unsigned long long)st.levels;
+    g->fsw = (unsigned long long)st.fsw;
+    g->isw[0] = (unsigned long long)st.isw;
+    g->lsw[0] = (unsigned long long)st.lsw;
+  }
+}
+
 // A streaming write over a buffer of `words` 16-byte words: evicts the L2
 // and the Infinity Cache before a cold-cache measurement.
 __global__ __launch_bounds__(256) void flush_kernel(uint4* buf, size_t words, uint32_t tag) {
@@ -493,6 +584,31 @@ hipError_t grid_solve_links(const Params& P, const ScenCtl& C, int j, hipStream_
   hipLaunchKernelGGL(exact_links_kernel, dim3(blocks), dim3(256), 0, s, P, C.l0, C.l1, j, P.xgrid);
   hipLaunchKernelGGL(exact_bottleneck_kernel, dim3(blocks), dim3(256), 0, s, P, C.l0, j, P.xgrid);
   return hipGetLastError();
+}
+
+bool grid_solve_fill_fits(const ScenCtl& C) {
+  return fill_bytes(C.l1 - C.l0, 0, false) <= FILL_DYNAMIC && C.l1 - C.l0 <= 65536;
+}
+
+hipError_t grid_solve_fill(const Params& P, const ScenCtl& C, int n, int max_rounds, hipStream_t s) {
+  const int nl = C.l1 - C.l0;
+  const int64_t bits = C.f1 > C.f0 ? (int64_t)(((C.f1 - 1) >> 5) - (C.f0 >> 5) + 1) * 32 : 0;
+  auto go = [&](auto kernel, size_t lds) {
+    hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(FILL_THREADS), lds, s, P, C.l0, C.l1, C.f0, C.f1, n, max_rounds,
+                       P.xgrid);
+    return hipGetLastError();
+  };
+  const size_t both = fill_bytes(nl, bits, true), with_bits = fill_bytes(nl, bits, false);
+  if (both <= FILL_DYNAMIC)
+    return C.lds_paths ? go(exact_fill_kernel<true, true, true>, both) : go(exact_fill_kernel<false, true, true>, both);
+  if (with_bits <= FILL_DYNAMIC)
+    return C.lds_paths ? go(exact_fill_kernel<true, true, false>, with_bits)
+                       : go(exact_fill_kernel<false, true, false>, with_bits);
+  const size_t none = fill_bytes(nl, 0, false);
+  return C.lds_paths ? go(exact_fill_kernel<true, false, false>, none)
+                     : go(exact_fill_kernel<false, false, false>, none);
 }
 
 int freeze_blocks(int n) {
