@@ -233,6 +233,9 @@ hipError_t launch_solve(const Params& p, int blocks, int threads, hipStream_t s)
 // pc pending flows in lds bytes of shared memory (wave_bytes of the largest part).
 hipError_t launch_wave(const Params& p, const int32_t* list, int parts, int sc, int pc, size_t lds, hipStream_t s);
 size_t wave_bytes(int nl, int nc, int sc, int pc);
+// The same for exact mode (xwave.hip).
+hipError_t launch_xwave(const Params& p, const int32_t* list, int parts, int sc, int pc, size_t lds, hipStream_t s);
+size_t xwave_bytes(int nl, int sc, int pc);
 hipError_t launch_grid(const Params& p, int blocks, int threads, hipStream_t s);
 // Largest co-resident grid for launch_grid at `threads` per block.
 hipError_t grid_capacity(int device, int threads, int* blocks);

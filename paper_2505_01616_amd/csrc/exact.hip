@@ -325,7 +325,8 @@ __device__ void exact_loop(const Params& P, int sc, XShared& sh, unsigned char* 
   int64_t rounds = resume ? C->rounds : 0;
   int64_t asw = resume ? C->active_swept : 0;
   int64_t psw = resume ? C->pending_swept : 0;
-  const int64_t events0 = events;
+  // the launch's limit counts the wave kernel's events too
+  const int64_t events0 = P.hand && resume ? events - C->launch_events : events;
   int rb = 0;
   int status = ST_DONE;
   if (tid == 0) {
@@ -337,7 +338,13 @@ __device__ void exact_loop(const Params& P, int sc, XShared& sh, unsigned char* 
   }
   __syncthreads();
   auto bad = [&](int f) { return (unsigned)(f - f0) >= (unsigned)cap; };
+  // a part the wave kernel left between an event's arrivals and its solve
+  if (resume && (C->mid & 2) != 0 && na > 0) {
+    status = exact_solve<LDS>(P, C, lk, sh, rb, act[ab], na, rounds);
+    solves += 1;
+  }
   for (;;) {
+    if (status != ST_DONE) break;
     if (na == 0 && np == 0) break;
     if (P.max_events > 0 && events - events0 >= P.max_events) {
       status = ST_STOPPED;
@@ -490,6 +497,7 @@ __device__ void exact_loop(const Params& P, int sc, XShared& sh, unsigned char* 
   __syncthreads();
   if (tid == 0) {
     C->started = 1;
+    C->mid = 0;
     C->t = t;
     C->ab = ab;
     C->e = pb;
@@ -537,13 +545,15 @@ __device__ void exact_solve_only(const Params& P, int sc, XShared& sh, unsigned 
 
 }  // namespace
 
-// One workgroup per part (a scenario: exact mode keeps one clock per
-// scenario).  A part whose link state fits the dynamic shared-memory pool
+// One workgroup per part of the launch's list (a scenario: exact mode keeps
+// one clock per scenario).  A part whose link state fits the dynamic shared-memory pool
 // keeps it there; the others use their slice of the global link arrays.
 __global__ __launch_bounds__(1024) void netsim_exact_kernel(Params P) {
   __shared__ XShared sh;
   extern __shared__ __align__(16) unsigned char xpool[];
-  for (int sc = blockIdx.x; sc < P.num_scen; sc += gridDim.x) {
+  const int parts = P.pcount ? *P.pcount : P.list ? P.num_list : P.num_scen;
+  for (int i = blockIdx.x; i < parts; i += gridDim.x) {
+    const int sc = P.list ? P.list[i] : i;
     const ScenCtl* C = &P.ctl[sc];
     const bool lds = (P.debug & DEBUG_EXACT_GLOBAL_LINKS) == 0 &&
                      (int64_t)(C->l1 - C->l0) * XLINK_BYTES <= (int64_t)P.exact_lds_bytes;
@@ -697,7 +707,8 @@ __device__ __forceinline__ void na_report(int status, int bad, int64_t levels, i
 // One workgroup: checks the input, then runs the exact solve over all F
 // flows.  Such a small solve is bound by its dozen dependent steps, so link
 // state goes to shared memory where it fits (LDS) and a few hundred flows take
-// 256 threads: 240 flows over 249 links SMALL_US.
+// 256 threads: 240 flows over 249 links 22.7 us before, 9.4 us so; 992 flows
+// over 569 links (1024 threads) 48.9 and 14.9 us.
 template <bool LDS>
 __global__ __launch_bounds__(1024) void netsim_noalloc_solve_kernel(const double* cap, int L,
                                                                     const int32_t* poff,

@@ -295,7 +295,9 @@ constexpr int kGridLevelBatch = 64;
 // Wave kernel: room for active and pending flows at most, and the classes of
 // parts by shared memory (32, 8 or fewer parts on a compute unit at once).
 constexpr int32_t kWaveSlots = 256, kWavePending = 512;
+constexpr int32_t kXWaveSlots = 512;  // exact mode (its solve's registers hold 8 x 64 flows)
 constexpr size_t kWaveClassBytes[] = {5 * 1024, 20 * 1024, 150 * 1024};
+constexpr int DEBUG_EXACT_GLOBAL = 16;  // options.debug bit 4: exact link state in global memory
 constexpr int DEBUG_EXACT_GRID = 32;  // options.debug bit 5: every such solve on the whole GPU
 
 netsim_status prepare(netsim_t* h) {
@@ -587,11 +589,14 @@ netsim_status prepare(netsim_t* h) {
   // the lists hold.  The others start in the block kernel.
   std::vector<int32_t> plist;
   h->wave.clear();
-  if (!exact) {
+  {
     constexpr size_t kClasses = sizeof kWaveClassBytes / sizeof kWaveClassBytes[0];
     std::vector<std::vector<int32_t>> in(kClasses);
     std::vector<netsim::WaveClass> wc(kClasses);
     std::vector<int32_t> big;
+    auto wave_size = [&](const ScenCtl& c, int32_t sc, int32_t pc) {
+      return exact ? netsim_dev::xwave_bytes(c.l1 - c.l0, sc, pc) : netsim_dev::wave_bytes(c.l1 - c.l0, c.nc, sc, pc);
+    };
     for (int32_t k = 0; k < NP; ++k) {
       const ScenCtl& c = ctl[(size_t)k];
       int32_t real = 0, roots = 0;
@@ -599,8 +604,8 @@ netsim_status prepare(netsim_t* h) {
         real += nbytes[(size_t)d] > 0.0;
         roots += nbytes[(size_t)d] > 0.0 && ndeps[(size_t)d] == 0;
       }
-      const int32_t sc = std::min(real, kWaveSlots), pc = std::min(c.f1 - c.f0, kWavePending);
-      const size_t z = netsim_dev::wave_bytes(c.l1 - c.l0, c.nc, sc, pc);
+      const int32_t sc = std::min(real, exact ? kXWaveSlots : kWaveSlots), pc = std::min(c.f1 - c.f0, kWavePending);
+      const size_t z = wave_size(c, sc, pc);
       size_t q = 0;
       while (q < kClasses && z > kWaveClassBytes[q]) ++q;
       if (!c.lds_paths || roots > sc || c.n_pend0 > pc || q == kClasses) {
@@ -619,8 +624,7 @@ netsim_status prepare(netsim_t* h) {
       // the class's lists are as long as its widest part's; what the links
       // take is added per part
       for (int32_t k : in[q])
-        wc[q].lds = std::max(wc[q].lds, netsim_dev::wave_bytes(ctl[(size_t)k].l1 - ctl[(size_t)k].l0,
-                                                               ctl[(size_t)k].nc, wc[q].sc, wc[q].pc));
+        wc[q].lds = std::max(wc[q].lds, wave_size(ctl[(size_t)k], wc[q].sc, wc[q].pc));
       plist.insert(plist.end(), in[q].begin(), in[q].end());
       h->wave.push_back(wc[q]);
     }
@@ -800,10 +804,13 @@ netsim_status reset_state(netsim_t* h, hipStream_t st) {
   return NETSIM_OK;
 }
 
-// The block layout's event loops: the small parts one wavefront each, the
-// others one workgroup each beside them (on a stream of the handle's own,
-// joined before the launch ends), then the parts the wave kernel handed over.
-hipError_t launch_event_loops(netsim_t* h, const Params& P0, int threads, hipStream_t st) {
+// The block layout's (or exact mode's) event loops: the small parts one
+// wavefront each, the others one workgroup each beside them (on a stream of
+// the handle's own, joined before the launch ends), then the parts the wave
+// kernel handed over.  big(P, parts, handed) launches the workgroup kernel over
+// at most `parts` parts of P.list.
+template <class Big>
+hipError_t launch_event_loops(netsim_t* h, const Params& P0, hipStream_t st, const Big& big) {
   Params P = P0;
   hipError_t he = hipSuccess;
   if (h->big_count > 0) {
@@ -816,13 +823,15 @@ hipError_t launch_event_loops(netsim_t* h, const Params& P0, int threads, hipStr
     if (he == hipSuccess) he = hipStreamWaitEvent(h->side, h->side_ev[0], 0);
     P.list = h->d_plist + h->big_first;
     P.num_list = h->big_count;
-    if (he == hipSuccess) he = netsim_dev::launch_block(P, std::min<int32_t>(h->big_count, 1 << 20), threads, h->side);
+    if (he == hipSuccess) he = big(P, h->big_count, false, h->side);
     if (he == hipSuccess) he = hipEventRecord(h->side_ev[1], h->side);
   }
   P.list = nullptr;
   int32_t unsafe = 0;
   for (const auto& w : h->wave) {
-    if (he == hipSuccess) he = netsim_dev::launch_wave(P, h->d_plist + w.first, w.count, w.sc, w.pc, w.lds, st);
+    if (he == hipSuccess)
+      he = (h->opt.exact ? netsim_dev::launch_xwave : netsim_dev::launch_wave)(P, h->d_plist + w.first, w.count, w.sc,
+                                                                             w.pc, w.lds, st);
     unsafe += w.unsafe;
   }
   if (he == hipSuccess && unsafe > 0) {
@@ -830,7 +839,7 @@ hipError_t launch_event_loops(netsim_t* h, const Params& P0, int threads, hipStr
     P.pcount = P.hcount;
     P.hand = 1;
     P.resume = 1;  // a part that has not started starts from t = 0
-    he = netsim_dev::launch_block(P, std::min<int32_t>(unsafe, 512), 512, st);
+    he = big(P, std::min<int32_t>(unsafe, 512), true, st);
   }
   if (he == hipSuccess && h->big_count > 0) he = hipStreamWaitEvent(st, h->side_ev[1], 0);
   return he;
@@ -910,7 +919,14 @@ netsim_status launch(netsim_t* h, hipStream_t st, bool solve_only, float* ms, bo
       int threads = h->opt.block_threads > 0 ? h->opt.block_threads : kExactThreads;
       threads = std::max(64, std::min(1024, threads / 64 * 64));
       const int blocks = std::max(1, std::min<int32_t>(S, 1 << 20));
-      he = netsim_dev::launch_exact(P, blocks, threads, st);
+      // a workgroup size asked for, and link state kept in global memory, are
+      // the workgroup kernel's
+      if (!solve_only && !h->wave.empty() && h->opt.block_threads == 0 && (h->opt.debug & DEBUG_EXACT_GLOBAL) == 0)
+        he = launch_event_loops(h, P, st, [&](const Params& Q, int parts, bool, hipStream_t s) {
+          return netsim_dev::launch_exact(Q, parts, threads, s);
+        });
+      else
+        he = netsim_dev::launch_exact(P, blocks, threads, st);
     } else if (exec == NETSIM_EXEC_CLUSTER) {
       int blocks = 0;
       he = netsim_dev::cluster_capacity(h->opt.device, &blocks);
@@ -946,7 +962,11 @@ netsim_status launch(netsim_t* h, hipStream_t st, bool solve_only, float* ms, bo
       if (solve_only)
         he = netsim_dev::launch_solve(P, blocks, threads, st);
       else if (!h->wave.empty() && h->opt.block_threads == 0 && (h->opt.debug & 1) == 0)
-        he = launch_event_loops(h, P, threads, st);
+        // (handed-over parts take the 512-thread kernel, which can start in
+        // the middle of an event)
+        he = launch_event_loops(h, P, st, [&](const Params& Q, int parts, bool handed, hipStream_t s) {
+          return netsim_dev::launch_block(Q, std::min(parts, 1 << 20), handed ? 512 : threads, s);
+        });
       else
         he = netsim_dev::launch_block(P, blocks, threads, st);
     }

@@ -1,0 +1,133 @@
+// What the kernels that run a part in one wavefront share (wave.hip: the
+// default solver, xwave.hip: exact mode).
+#pragma once
+
+#include "device.h"
+#include "lanes.h"
+
+#include <math.h>
+
+#pragma clang fp contract(off)
+
+namespace netsim_dev {
+
+namespace {
+
+constexpr double WTHR = 1.000000000001;
+constexpr double WINF = __builtin_huge_val();
+
+// Orders this wave's shared-memory accesses for the compiler; the hardware
+// performs a wave's LDS operations in order.
+__device__ __forceinline__ void wsync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ int64_t wsum(int64_t v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+template <class T>
+__device__ __forceinline__ void ladd(T* p, T v) {
+  __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Finished flows whose successors are still to be counted down: a log of
+// flow ids in global memory (a flow finishes once, so it never overflows) and
+// the newest WQ entries with their successor range in shared memory.
+constexpr int WQ = 64;
+struct Done {
+  int32_t k0, k1;
+  double fin;
+};
+
+// A flow's own data, read when it is released.
+struct Own {
+  double nb;
+  uint4 rec;
+  int k0, k1, comp;
+};
+
+__device__ __forceinline__ Own own_of(const Params& P, int f) {
+  Own o;
+  o.nb = P.nbytes[f];
+  o.rec = P.path16[f];
+  o.k0 = P.soff[f];
+  o.k1 = P.soff[f + 1];
+  o.comp = P.comp[f];
+  return o;
+}
+
+// Unpacks a path record into part-local link ids; an absent link becomes the
+// sentinel entry nl (share +inf, never stamped).  Returns the degree.
+__device__ __forceinline__ int unpack(const uint4 rec, int nl, int* lv) {
+  const uint32_t w[3] = {rec.x, rec.y, rec.z};
+  int deg = 0;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    const int u = (int)((w[k >> 1] >> (16 * (k & 1))) & 0xFFFFu);
+    deg += u != 0xFFFF;
+    lv[k] = min(u, nl);
+  }
+  return deg;
+}
+
+// The log of one event's finished flows.
+struct WaveLog {
+  const Params& P;
+  const int lane, f0;
+  Done* ring;       // [WQ], shared memory
+  int qh = 0, qt = 0;  // entries handled, entries
+
+  __device__ __forceinline__ WaveLog(const Params& P_, int first) : P(P_), lane((int)threadIdx.x), f0(first) {}
+
+  // A finished flow joins the log (all lanes call it).
+  __device__ __forceinline__ void push(bool p, int f, int a, int b, double fin) {
+    const uint64_t m = __ballot(p);
+    if (m == 0) return;
+    if (p) {
+      const int q = qt + rank_in(m);
+      ring[q & (WQ - 1)] = Done{a, b, fin};
+      P.comp0[f0 + q] = f;
+    }
+    qt += (int)__popcll(m);
+  }
+
+  // body(in, k, fin) for every successor index of the logged flows
+  // [qh, qh + cnt): lane by lane when the ranges are short, else range by
+  // range over the whole wave.
+  template <class Body>
+  __device__ __forceinline__ void successors(int cnt, Body body) {
+    int a = 0, b = 0;
+    double fin = 0.0;
+    if (lane < cnt) {
+      const int q = qh + lane;
+      if (qt - q <= WQ) {
+        const Done d = ring[q & (WQ - 1)];
+        a = d.k0;
+        b = d.k1;
+        fin = d.fin;
+      } else {
+        const int f = P.comp0[f0 + q];
+        a = P.soff[f];
+        b = P.soff[f + 1];
+        if (P.lat) fin = P.finish[f];
+      }
+    }
+    if (__ballot(b - a > 8) == 0) {
+      for (; __ballot(a < b) != 0; ++a) body(a < b, a, fin);
+      return;
+    }
+    for (int j = 0; j < cnt; ++j) {
+      const int z = __shfl(b, j, 64);
+      const double fj = __shfl(fin, j, 64);
+      for (int k = __shfl(a, j, 64); k < z; k += 64) body(k + lane < z, k + lane, fj);
+    }
+  }
+};
+
+}  // namespace
+
+}  // namespace netsim_dev

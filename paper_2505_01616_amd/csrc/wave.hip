@@ -29,10 +29,7 @@
 // handed over to the block kernel at that event (its state written out as
 // the event loop's own position, see ScenCtl::mid), which wins once there are
 // several hundred flows per sweep.
-#include "device.h"
-#include "lanes.h"
-
-#include <math.h>
+#include "wave.h"
 
 #pragma clang fp contract(off)
 
@@ -40,72 +37,11 @@ namespace netsim_dev {
 
 namespace {
 
-constexpr double WTHR = 1.000000000001;
 constexpr double WKEEP = 1.0 - 1e-9;
-constexpr double WINF = __builtin_huge_val();
 
-// Orders this wave's shared-memory accesses for the compiler; the hardware
-// performs a wave's LDS operations in order.
-__device__ __forceinline__ void wsync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-__device__ __forceinline__ int64_t wsum(int64_t v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-template <class T>
-__device__ __forceinline__ void ladd(T* p, T v) {
-  __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Finished flows whose successors are still to be counted down: a log of
-// flow ids in global memory (a flow finishes once, so it never overflows) and
-// the newest WQ entries with their successor range in shared memory.
-constexpr int WQ = 64;
-struct Done {
-  int32_t k0, k1;
-  double fin;
-};
-
-// A flow's own data, read when it is released.
-struct Own {
-  double nb;
-  uint4 rec;
-  int k0, k1, comp;
-};
-
-__device__ __forceinline__ Own own_of(const Params& P, int f) {
-  Own o;
-  o.nb = P.nbytes[f];
-  o.rec = P.path16[f];
-  o.k0 = P.soff[f];
-  o.k1 = P.soff[f + 1];
-  o.comp = P.comp[f];
-  return o;
-}
-
-// Unpacks a path record into part-local link ids; an absent link becomes the
-// sentinel entry nl (share +inf, never stamped).  Returns the degree.
-__device__ __forceinline__ int unpack(const uint4 rec, int nl, int* lv) {
-  const uint32_t w[3] = {rec.x, rec.y, rec.z};
-  int deg = 0;
-#pragma unroll
-  for (int k = 0; k < 6; ++k) {
-    const int u = (int)((w[k >> 1] >> (16 * (k & 1))) & 0xFFFFu);
-    deg += u != 0xFFFF;
-    lv[k] = min(u, nl);
-  }
-  return deg;
-}
-
-struct Wave {
-  const Params& P;
+struct Wave : WaveLog {
   ScenCtl* C;
-  const int lane, f0, nl, sc, pc;
+  const int nl, sc, pc;
   const bool hist;  // the rollback history is kept
   // shared memory
   int64_t* R;      // [nl + 1] residual capacity
@@ -122,11 +58,10 @@ struct Wave {
   uint16_t *sel, *freed;            // [sc] re-solve list (before it: new flows), free slots
   double* prel;    // [pc] pending flows: release time
   int32_t* pid;    // [pc]
-  Done* ring;      // [WQ]
   // the same in every lane
   int nSlots = 0, nFree = 0, nPend = 0, nArr = 0;
   int nSpill = 0, pSpill = 0;       // new and pending flows beyond the lists
-  int qh = 0, qt = 0, ndone = 0;    // finished-flow log; flows that left their links in this event
+  int ndone = 0;                    // flows that left their links in this event
   int vS = 0, vH = 0;               // slots and holes as the block kernel's layout has them
   int e = 0;
   double t = 0.0;
@@ -139,7 +74,7 @@ struct Wave {
   }
 
   __device__ __forceinline__ Wave(const Params& P_, ScenCtl* C_, unsigned char* pool, int sc_, int pc_)
-      : P(P_), C(C_), lane((int)threadIdx.x), f0(C_->f0), nl(C_->l1 - C_->l0), sc(sc_), pc(pc_),
+      : WaveLog(P_, C_->f0), C(C_), nl(C_->l1 - C_->l0), sc(sc_), pc(pc_),
         hist(P_.hist != nullptr && C_->hcap > 0) {
     const int l = (nl + 1 + 7) & ~7, s = (sc + 7) & ~7, p = (pc + 7) & ~7;
     unsigned char* b = pool;
@@ -170,18 +105,6 @@ struct Wave {
     ll = reinterpret_cast<uint16_t*>(take((size_t)l * 2));
     sel = reinterpret_cast<uint16_t*>(take((size_t)s * 2));
     freed = reinterpret_cast<uint16_t*>(take((size_t)s * 2));
-  }
-
-  // A finished flow joins the log (all lanes call it).
-  __device__ __forceinline__ void push(bool p, int f, int a, int b, double fin) {
-    const uint64_t m = __ballot(p);
-    if (m == 0) return;
-    if (p) {
-      const int q = qt + rank_in(m);
-      ring[q & (WQ - 1)] = Done{a, b, fin};
-      P.comp0[f0 + q] = f;
-    }
-    qt += (int)__popcll(m);
   }
 
   // Flow f becomes active at time t (all lanes call it).
@@ -269,38 +192,6 @@ struct Wave {
       const int over = max(0, nPend + c - pc);
       nPend = min(nPend + c, pc);
       pSpill += over;
-    }
-  }
-
-  // body(in, k, fin) for every successor index of the logged flows
-  // [qh, qh + cnt): lane by lane when the ranges are short, else range by
-  // range over the whole wave.
-  template <class Body>
-  __device__ __forceinline__ void successors(int cnt, Body body) {
-    int a = 0, b = 0;
-    double fin = 0.0;
-    if (lane < cnt) {
-      const int q = qh + lane;
-      if (qt - q <= WQ) {
-        const Done d = ring[q & (WQ - 1)];
-        a = d.k0;
-        b = d.k1;
-        fin = d.fin;
-      } else {
-        const int f = P.comp0[f0 + q];
-        a = P.soff[f];
-        b = P.soff[f + 1];
-        if (P.lat) fin = P.finish[f];
-      }
-    }
-    if (__ballot(b - a > 8) == 0) {
-      for (; __ballot(a < b) != 0; ++a) body(a < b, a, fin);
-      return;
-    }
-    for (int j = 0; j < cnt; ++j) {
-      const int z = __shfl(b, j, 64);
-      const double fj = __shfl(fin, j, 64);
-      for (int k = __shfl(a, j, 64); k < z; k += 64) body(k + lane < z, k + lane, fj);
     }
   }
 
@@ -453,6 +344,46 @@ struct Wave {
       if (++r > P.max_rounds) return ST_ROUNDS;
       total = left;
     }
+  }
+
+  // Active flows to the front of the slots (every sweep looks at all slots).
+  __device__ __forceinline__ void compact() {
+    int keep = 0;
+    for (int s0 = 0; s0 < nSlots; s0 += 64) {
+      const int s = s0 + lane;
+      const int f = s < nSlots ? id[s] : -1;
+      uint4 p{};
+      double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
+      int x = 0, y = 0, z = 0;
+      if (f >= 0) {
+        p = path[s];
+        a = tau[s];
+        b = rate[s];
+        c = rem[s];
+        d = tref[s];
+        x = k0[s];
+        y = k1[s];
+        z = comp[s];
+      }
+      wsync();
+      const uint64_t m = __ballot(f >= 0);
+      if (f >= 0) {
+        const int to = keep + rank_in(m);
+        path[to] = p;
+        tau[to] = a;
+        rate[to] = b;
+        rem[to] = c;
+        tref[to] = d;
+        id[to] = f;
+        k0[to] = x;
+        k1[to] = y;
+        comp[to] = z;
+      }
+      keep += (int)__popcll(m);
+      wsync();
+    }
+    nSlots = keep;
+    nFree = 0;
   }
 
   // Reads the position a launch left (or the start), if the lists hold it.
@@ -807,6 +738,7 @@ __device__ __forceinline__ void wave_loop(const Params& P, int part, int sc, int
       w.vH = 0;
     }
     if (w.nFree == w.nSlots) w.nFree = w.nSlots = 0;
+    else if (w.nFree >= 64) w.compact();
     if (hist && lane == 0) {
       HistEv r;
       r.t = w.t;

@@ -1,7 +1,7 @@
-"""GPU tests of the block layout's one-wave kernel against its workgroup
-kernel (block_threads asks for the latter): finish times and statistics bit
-for bit, at the edges of the wave kernel's lists (256 active and 512 pending
-flows, 64 finished flows at once), where a part is handed over in the middle
+"""GPU tests of the one-wave kernels (block layout, exact mode) against the
+workgroup kernels (block_threads asks for the latter): finish times and statistics bit
+for bit, at the edges of the wave kernels' lists (256, exact mode 512 active and 512
+pending flows, 64 finished flows at once), where a part is handed over in the middle
 of an event, and when the run is advanced in pieces across the hand-over."""
 
 import sys
@@ -70,6 +70,33 @@ def test_hand_over(n, lagged, latency):
         assert sa[k] == sb[k], (k, sa[k], sb[k])
     want = osim.run_scenario(program.scenarios[0]).finish
     assert np.max(np.abs(a[0] - want) / want) < 1e-9
+
+
+@pytest.mark.parametrize("latency", [False, True])
+@pytest.mark.parametrize("n,lagged", [(120, False), (129, False), (511, False), (512, False), (513, False),
+                                      (700, False), (512, True), (513, True), (1500, True)])
+def test_exact_hand_over(n, lagged, latency):
+    """Exact mode: bit for bit the oracle, in one run and advanced in pieces
+    across the hand-over, with the workgroup kernel's counters."""
+    ns, pr = _gpu()
+    program = _release(n, lagged, latency)
+    _say(f"test_exact_hand_over n={n} lagged={lagged} latency={latency}")
+    want = osim.run_scenario(program.scenarios[0])
+    a, sa = pr.run_program(program, ns.make_options(exact=1))
+    b, sb = pr.run_program(program, ns.make_options(exact=1, block_threads=512))
+    assert np.array_equal(a[0], want.finish) and np.array_equal(b[0], want.finish)
+    for k in SAME:
+        assert sa[k] == sb[k], (k, sa[k], sb[k])
+    assert (sa["events"], sa["solves"], sa["rounds"]) == (want.events, want.solves, want.iterations)
+    ld = pr.load_program(program, ns.make_options(exact=1))
+    try:
+        for _ in range(200):
+            ns.netsim_advance(ld.handle, max_events=41)
+            if ns.netsim_get_stats(ld.handle)["complete"]:
+                break
+        assert np.array_equal(ns.netsim_get_finish(ld.handle), want.finish)
+    finally:
+        ld.close()
 
 
 @pytest.mark.parametrize("history", [0, 8])
