@@ -10,7 +10,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnetsim.so")
-SOURCES = ["netsim.cpp", "fabric.cpp", "kernels.hip", "wave.hip", "xwave.hip", "exact.hip", "sweep.hip", "history.hip"]
+SOURCES = ["netsim.cpp", "fabric.cpp", "kernels.hip", "wave.hip", "xwave.hip", "exact.hip", "sweep.hip", "history.hip",
+           "results.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [

@@ -226,6 +226,40 @@ struct Params {
 constexpr int BAR_WORDS = 9216 + 64 * 32 * 32;
 constexpr int BAR_HAND = 50;  // parts the wave kernel has handed over (Params::hcount)
 
+// The state at t = 0, kept on the device (results.hip).
+struct Initial {
+  const int32_t* cnt;
+  const double* rel;
+  const int32_t* pend;
+  const ScenCtl* ctl;
+};
+// Results of a launch, gathered in one block: totals over the parts, then
+// makespan (bits of a double) per scenario, time reached per part (-inf: not
+// started), finish time per flow in id order.
+struct RunTotals {
+  static constexpr int kCounts = 12;
+  int64_t count[kCounts];  // events, solves, rounds, flows, incidences, active and pending swept,
+                           // reselected, wide, assisted, links swept, launch events
+  uint64_t t;              // largest time reached (bits of a double)
+  int64_t stopped, faults; // parts that did not run to their end, parts with a fault
+  int64_t completed;       // flows with a finish time
+  int64_t ticks[8];
+};
+struct Results {
+  RunTotals* totals;
+  uint64_t* makespan;
+  double* part_t;
+  double* finish;
+};
+hipError_t launch_reset(const Params& P, const Initial& I, int64_t F, int64_t L, int NP, hipStream_t s);
+hipError_t launch_reset_words(const Params& P, const Results& R, int scenarios, hipStream_t s);
+hipError_t launch_results(const Params& P, const Results& R, const int32_t* dev_of, const int32_t* scen_of, int64_t F,
+                          hipStream_t s);
+// Active counts of the links of the n listed flows (P.nact zero before), and
+// the listed flows' rates.
+hipError_t launch_count_active(const Params& P, const int32_t* list, int n, hipStream_t s);
+hipError_t launch_gather_rates(const Params& P, const int32_t* list, int n, double* out, hipStream_t s);
+
 hipError_t launch_block(const Params& p, int blocks, int threads, hipStream_t s);
 // Params::mode 1: one rate solve per part, one workgroup per part.
 hipError_t launch_solve(const Params& p, int blocks, int threads, hipStream_t s);

@@ -98,8 +98,20 @@ struct netsim {
   std::vector<Checkpoint> checkpoints;
   std::vector<double> part_t;         // per part: time of its last processed event (-inf: none)
   Params prm{};
-  // results
-  std::vector<double> finish;         // id order
+  // state at t = 0 and the results block on the device, and its copy on the
+  // host (pinned where that memory can be had): kept for the handle's life
+  netsim_dev::Initial init{};
+  netsim_dev::Results res{};
+  size_t res_bytes = 0;
+  char* host = nullptr;
+  bool host_pinned = false;
+  int32_t* d_dev_of = nullptr;        // id -> device flow
+  int32_t* d_active = nullptr;        // device flows of a single rate solve
+  int32_t* d_scen_of = nullptr;       // id -> scenario (NULL: one scenario)
+  int64_t widest = 0;                 // flows without predecessors in the widest part
+  hipEvent_t ev[2] = {};              // around a launch
+  const char* at_host(const void* dev) const { return host + ((const char*)dev - (const char*)res.totals); }
+  const double* finish() const { return (const double*)at_host(res.finish); }  // id order
   std::vector<double> makespan;
   netsim_stats stats{};
 };
@@ -636,6 +648,7 @@ netsim_status prepare(netsim_t* h) {
   // one device allocation, carved into aligned arrays
   const size_t Fz = (size_t)std::max<int64_t>(F, 1), Lz = (size_t)std::max<int64_t>(ld, 1);
   const size_t XL = h->opt.exact ? Lz : 1;
+  h->res_bytes = sizeof(netsim_dev::RunTotals) + sizeof(double) * ((size_t)S + (size_t)NP + Fz);
   struct Part { void** dst; size_t bytes; };
   Params& P = h->prm;
   P = Params{};
@@ -686,6 +699,14 @@ netsim_status prepare(netsim_t* h) {
       {(void**)&P.unf1, sizeof(int32_t) * Fz},
       {(void**)&P.bar, sizeof(uint32_t) * netsim_dev::BAR_WORDS},
       {(void**)&P.slots, sizeof(uint64_t) * 8},
+      {(void**)&h->init.cnt, sizeof(int32_t) * Fz},
+      {(void**)&h->init.rel, sizeof(double) * Fz},
+      {(void**)&h->init.pend, sizeof(int32_t) * Fz},
+      {(void**)&h->init.ctl, sizeof(ScenCtl) * (size_t)std::max<int32_t>(NP, 1)},
+      {(void**)&h->d_dev_of, sizeof(int32_t) * Fz},
+      {(void**)&h->d_active, sizeof(int32_t) * Fz},
+      {(void**)&h->d_scen_of, sizeof(int32_t) * (S > 1 ? Fz : 1)},
+      {(void**)&h->res.totals, h->res_bytes},
       {(void**)&h->d_plist, sizeof(int32_t) * plist.size()},
       {(void**)&P.hlist, sizeof(int32_t) * plist.size()},
       // exact mode: link state in fp64 (one element each otherwise)
@@ -719,6 +740,22 @@ netsim_status prepare(netsim_t* h) {
     *p.dst = base;
     base += (p.bytes + 255) & ~size_t(255);
   }
+  h->res.makespan = (uint64_t*)(h->res.totals + 1);
+  h->res.part_t = (double*)(h->res.makespan + S);
+  h->res.finish = h->res.part_t + NP;
+  if (hipHostMalloc((void**)&h->host, h->res_bytes, hipHostMallocDefault) == hipSuccess) {
+    h->host_pinned = true;
+  } else {
+    (void)hipGetLastError();
+    h->host = new (std::nothrow) char[h->res_bytes];
+    if (!h->host) return fail(h, NETSIM_E_NOMEM, "no host memory for the results");
+  }
+  for (auto& e : h->ev) {
+    he = hipEventCreate(&e);
+    if (he != hipSuccess) return hip_fail(h, he, "hipEventCreate");
+  }
+  h->widest = 0;
+  for (const ScenCtl& c : h->h_ctl0) h->widest = std::max<int64_t>(h->widest, c.n_pend0);
   h->persist = (char*)P.rem;
   h->persist_bytes = (size_t)((char*)P.ctl - (char*)P.rem) + sizeof(ScenCtl) * (size_t)std::max<int32_t>(NP, 1);
   if (hist_bytes > 0) {
@@ -748,6 +785,12 @@ netsim_status prepare(netsim_t* h) {
       {lat.data(), P.lat, any_lat ? sizeof(double) * lat.size() : 0},
       {capf.data(), P.capf, h->opt.exact ? sizeof(double) * capf.size() : 0},
       {plist.data(), h->d_plist, sizeof(int32_t) * plist.size()},
+      {h->h_cnt0.data(), h->init.cnt, sizeof(int32_t) * Fz},
+      {h->h_rel0.data(), h->init.rel, sizeof(double) * Fz},
+      {h->h_pend0.data(), h->init.pend, sizeof(int32_t) * Fz},
+      {h->h_ctl0.data(), h->init.ctl, sizeof(ScenCtl) * h->h_ctl0.size()},
+      {h->dev_of_flow.data(), h->d_dev_of, sizeof(int32_t) * (size_t)F},
+      {h->f_scen.data(), h->d_scen_of, S > 1 ? sizeof(int32_t) * (size_t)F : 0},
       {lfoff.data(), P.lfoff, sizeof(int32_t) * lfoff.size()},
       {lfid.data(), P.lfid, sizeof(int32_t) * lfid.size()},
       {lfchunk.data(), P.lfchunk, sizeof(int32_t) * lfchunk.size()},
@@ -759,6 +802,7 @@ netsim_status prepare(netsim_t* h) {
     if (he != hipSuccess) return hip_fail(h, he, "hipMemcpy (upload)");
   }
   if (!any_lat) P.lat = nullptr;  // no latency anywhere: arrival = last byte
+  if (S == 1) h->d_scen_of = nullptr;
   P.hcount = reinterpret_cast<int32_t*>(P.bar + netsim_dev::BAR_HAND);
   P.num_scen = NP;
   P.scale = h->scale;
@@ -767,41 +811,11 @@ netsim_status prepare(netsim_t* h) {
   return NETSIM_OK;
 }
 
-// Resets the dynamic state for a run from t = 0 (on `stream`).
+// Resets the dynamic state for a run from t = 0 (on `stream`, in its order).
 netsim_status reset_state(netsim_t* h, hipStream_t st) {
-  Params& P = h->prm;
-  const size_t Fz = (size_t)std::max<int64_t>(h->F, 1), Lz = (size_t)std::max<int64_t>(h->L, 1);
-  hipError_t he;
-  std::vector<double> nan((size_t)Fz, std::numeric_limits<double>::quiet_NaN());
-  const uint64_t inf_bits = 0x7FF0000000000000ull;
-  uint64_t slots[8];
-  for (auto& x : slots) x = inf_bits;
-  struct Up { const void* src; void* dst; size_t bytes; };
-  const Up ups[] = {
-      {h->h_cnt0.data(), P.cnt, sizeof(int32_t) * Fz},
-      {h->h_rel0.data(), P.rel, sizeof(double) * Fz},
-      {h->h_pend0.data(), P.pend0, sizeof(int32_t) * Fz},
-      {nan.data(), P.finish, sizeof(double) * Fz},
-      {h->h_ctl0.data(), P.ctl, sizeof(ScenCtl) * h->h_ctl0.size()},
-      {slots, P.slots, sizeof(slots)},
-  };
-  for (const Up& u : ups) {
-    if (u.bytes == 0) continue;
-    he = hipMemcpyAsync(u.dst, u.src, u.bytes, hipMemcpyHostToDevice, st);
-    if (he != hipSuccess) return hip_fail(h, he, "hipMemcpyAsync (reset)");
-  }
-  h->hist_ok = P.hist != nullptr;
-  he = hipMemsetAsync(P.nact, 0, sizeof(int32_t) * Lz, st);
-  // per-flow event indices: EV_NEVER, every byte 0x7F
-  for (int32_t* a : {P.evr, P.eva, P.evd})
-    if (he == hipSuccess) he = hipMemsetAsync(a, 0x7F, sizeof(int32_t) * Fz, st);
-  if (he == hipSuccess) he = hipMemsetAsync(P.base, 0, sizeof(double) * Fz, st);
-  if (he == hipSuccess) he = hipMemsetAsync(P.rate, 0, sizeof(double) * Fz, st);
-  if (he == hipSuccess) he = hipMemsetAsync(P.bar, 0, sizeof(uint32_t) * netsim_dev::BAR_WORDS, st);
-  if (he != hipSuccess) return hip_fail(h, he, "hipMemsetAsync (reset)");
-  he = hipStreamSynchronize(st);
-  if (he != hipSuccess) return hip_fail(h, he, "hipStreamSynchronize (reset)");
-  return NETSIM_OK;
+  h->hist_ok = h->prm.hist != nullptr;
+  const hipError_t he = netsim_dev::launch_reset(h->prm, h->init, h->F, h->L, h->num_parts, st);
+  return he == hipSuccess ? NETSIM_OK : hip_fail(h, he, "reset of the state");
 }
 
 // The block layout's (or exact mode's) event loops: the small parts one
@@ -866,12 +880,7 @@ netsim_status launch(netsim_t* h, hipStream_t st, bool solve_only, float* ms, bo
   int exec = h->opt.exec;
   // flows without predecessors in the widest part (a part whose flows chain
   // through dependencies keeps few of them active at once, however many it has)
-  int64_t widest = 0;
-  for (const ScenCtl& c : h->h_ctl0) {
-    int64_t roots = 0;
-    for (int32_t d = c.f0; d < c.f1; ++d) roots += h->h_cnt0[(size_t)d] == 0;
-    widest = std::max(widest, roots);
-  }
+  const int64_t widest = h->widest;
   if (exec == NETSIM_EXEC_AUTO) {
     // the whole GPU on one part when its first solve alone exceeds what one
     // workgroup solves in shared memory (more than 64 x 1024 flows); the
@@ -894,15 +903,9 @@ netsim_status launch(netsim_t* h, hipStream_t st, bool solve_only, float* ms, bo
   if (!solve_only && (exec == NETSIM_EXEC_CLUSTER || exec == NETSIM_EXEC_EXACT)) h->hist_ok = false;
   // grid-barrier words and min-reduction slots start fresh in every launch
   // (a launch that continues a run must not see the last launch's counts)
-  uint64_t inf_slots[8];
-  for (auto& x : inf_slots) x = 0x7FF0000000000000ull;
-  hipError_t he = hipMemsetAsync(P.bar, 0, sizeof(uint32_t) * netsim_dev::BAR_WORDS, st);
-  if (he == hipSuccess) he = hipMemcpyAsync(P.slots, inf_slots, sizeof(inf_slots), hipMemcpyHostToDevice, st);
+  hipError_t he = netsim_dev::launch_reset_words(P, h->res, (int)h->scen.size(), st);
   if (he != hipSuccess) return hip_fail(h, he, "reset of the grid synchronisation words");
-  hipEvent_t e0, e1;
-  he = hipEventCreate(&e0);
-  if (he == hipSuccess) he = hipEventCreate(&e1);
-  if (he != hipSuccess) return hip_fail(h, he, "hipEventCreate");
+  const hipEvent_t e0 = h->ev[0], e1 = h->ev[1];
   he = hipEventRecord(e0, st);
   if (he == hipSuccess) {
     if (exec == NETSIM_EXEC_EXACT) {
@@ -972,10 +975,14 @@ netsim_status launch(netsim_t* h, hipStream_t st, bool solve_only, float* ms, bo
     }
   }
   if (he == hipSuccess) he = hipEventRecord(e1, st);
+  if (he == hipSuccess && !solve_only) {
+    // results into one block, and that to the host, before the one wait
+    he = netsim_dev::launch_results(P, h->res, h->d_dev_of, h->d_scen_of, h->F, st);
+    if (he == hipSuccess) he = hipMemcpyAsync(h->host, h->res.totals, h->res_bytes, hipMemcpyDeviceToHost, st);
+    if (he == hipSuccess) he = hipStreamSynchronize(st);
+  }
   if (he == hipSuccess) he = hipEventSynchronize(e1);
   if (he == hipSuccess) he = hipEventElapsedTime(ms, e0, e1);
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
   if (he != hipSuccess) return hip_fail(h, he, "kernel launch");
   return NETSIM_OK;
 }
@@ -1033,57 +1040,47 @@ netsim_status simulate(netsim_t* h, hipStream_t st, bool resume, int64_t max_eve
   if (h->F > 0) {
     rc = launch(h, st, false, &ms, resume, max_events, until);
     if (rc) return rc;
+  } else {
+    he = hipStreamSynchronize(st);
+    if (he != hipSuccess) return hip_fail(h, he, "hipStreamSynchronize (reset)");
   }
   h->has_state = true;
-  std::vector<ScenCtl> ctl;
-  rc = h->F > 0 ? collect(h, &ctl) : NETSIM_OK;
-  if (h->F == 0) ctl = h->h_ctl0;
   // results, even on a device fault (partial), for inspection
-  const int64_t F = h->F;
-  std::vector<double> fin_dev((size_t)std::max<int64_t>(F, 1));
-  if (F > 0) {
-    he = hipMemcpy(fin_dev.data(), h->prm.finish, sizeof(double) * (size_t)F, hipMemcpyDeviceToHost);
-    if (he != hipSuccess) return hip_fail(h, he, "hipMemcpy (finish)");
-  }
-  h->finish.assign((size_t)F, 0.0);
-  for (int64_t id = 0; id < F; ++id) h->finish[(size_t)id] = fin_dev[(size_t)h->dev_of_flow[(size_t)id]];
-  h->makespan.assign(h->scen.size(), 0.0);
+  const int32_t S = (int32_t)h->scen.size(), NP = h->num_parts;
+  h->makespan.assign((size_t)S, 0.0);
+  h->part_t.assign((size_t)NP, -std::numeric_limits<double>::infinity());
   netsim_stats s{};
   s.complete = 1;
-  s.parts = h->num_parts;
-  const int32_t NP = h->num_parts;
-  h->part_t.assign((size_t)NP, -std::numeric_limits<double>::infinity());
-  for (int32_t k = 0; k < NP; ++k)
-    if (ctl[(size_t)k].started) h->part_t[(size_t)k] = ctl[(size_t)k].t;
-  for (int32_t k = 0; k < NP; ++k) {
-    const ScenCtl& c = ctl[(size_t)k];
-    double& m = h->makespan[(size_t)c.scen];
-    for (int32_t d = c.f0; d < c.f1; ++d)
-      if (!std::isnan(fin_dev[(size_t)d])) {
-        m = std::max(m, fin_dev[(size_t)d]);
-        s.completed_flows += 1;
-      }
-    s.events += c.events;
-    s.solves += c.solves;
-    s.rounds += c.rounds;
-    s.flows_swept += c.flows_swept;
-    s.incidences_swept += c.incidences_swept;
-    s.active_swept += c.active_swept;
-    s.pending_swept += c.pending_swept;
-    s.reselected += c.reselected;
-    s.wide_solves += c.wide_solves;
-    s.assisted_solves += c.assisted;
-    s.links_swept += c.links_swept;
-    s.launch_events += c.launch_events;
+  s.parts = NP;
+  if (h->F > 0) {
+    const netsim_dev::RunTotals& t = *(const netsim_dev::RunTotals*)h->host;
+    std::memcpy(h->makespan.data(), h->at_host(h->res.makespan), sizeof(double) * (size_t)S);
+    std::memcpy(h->part_t.data(), h->at_host(h->res.part_t), sizeof(double) * (size_t)NP);
+    s.events = t.count[0];
+    s.solves = t.count[1];
+    s.rounds = t.count[2];
+    s.flows_swept = t.count[3];
+    s.incidences_swept = t.count[4];
+    s.active_swept = t.count[5];
+    s.pending_swept = t.count[6];
+    s.reselected = t.count[7];
+    s.wide_solves = t.count[8];
+    s.assisted_solves = t.count[9];
+    s.links_swept = t.count[10];
+    s.launch_events = t.count[11];
+    s.completed_flows = t.completed;
     s.layout = h->layout;
-    s.sim_time = std::max(s.sim_time, c.t);
-    if (c.status != 0) s.complete = 0;
+    std::memcpy(&s.sim_time, &t.t, sizeof(double));
+    if (t.stopped > 0) s.complete = 0;
+    int khz = 0;
+    if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, h->opt.device) != hipSuccess || khz <= 0)
+      khz = 100000;
+    for (int j = 0; j < 8; ++j) s.phase_seconds[j] = (double)t.ticks[j] / (1e3 * khz);
+    if (t.faults > 0) {
+      std::vector<ScenCtl> ctl;
+      rc = collect(h, &ctl);  // which part, and why
+    }
   }
-  int khz = 0;
-  if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, h->opt.device) != hipSuccess || khz <= 0)
-    khz = 100000;
-  for (int32_t k = 0; k < NP; ++k)
-    for (int j = 0; j < 8; ++j) s.phase_seconds[j] += (double)ctl[(size_t)k].ticks[j] / (1e3 * khz);
   s.device_seconds = ms * 1e-3;
   s.upload_seconds = std::chrono::duration<double>(t1 - t0).count();
   h->stats = s;
@@ -2102,7 +2099,7 @@ netsim_status netsim_get_finish(const netsim_t* h, double* finish, double* makes
   if (!h) return fail(nullptr, NETSIM_E_INVALID, "get_finish: handle is NULL");
   if (!h->has_result) return fail(h, NETSIM_E_STATE, "get_finish: no run yet");
   if (!finish && h->F > 0) return fail(h, NETSIM_E_INVALID, "get_finish: finish is NULL");
-  std::copy(h->finish.begin(), h->finish.end(), finish);
+  if (h->F > 0) std::copy(h->finish(), h->finish() + h->F, finish);
   if (makespan) std::copy(h->makespan.begin(), h->makespan.end(), makespan);
   return NETSIM_OK;
 }
@@ -2112,7 +2109,7 @@ netsim_status netsim_get_finish_device(const netsim_t* h, double* d_finish) {
   if (!h->has_result) return fail(h, NETSIM_E_STATE, "get_finish_device: no run yet");
   if (h->F == 0) return NETSIM_OK;
   if (!d_finish) return fail(h, NETSIM_E_INVALID, "get_finish_device: pointer is NULL");
-  hipError_t he = hipMemcpy(d_finish, h->finish.data(), sizeof(double) * (size_t)h->F, hipMemcpyHostToDevice);
+  hipError_t he = hipMemcpy(d_finish, h->finish(), sizeof(double) * (size_t)h->F, hipMemcpyHostToDevice);
   if (he != hipSuccess) return hip_fail(h, he, "hipMemcpy (finish to device)");
   return NETSIM_OK;
 }
@@ -2166,15 +2163,11 @@ netsim_status netsim_solve_once(netsim_t* h, int32_t scen, int64_t n_active, con
   std::vector<int32_t> list((size_t)std::max<int64_t>(h->F, 1));
   std::vector<int32_t> dev((size_t)std::max<int64_t>(n_active, 1));
   std::vector<int32_t> fill((size_t)std::max<int32_t>(h->num_parts, 1), 0);
-  std::vector<int32_t> nact((size_t)std::max<int64_t>(h->L, 1), 0);
   for (int64_t k = 0; k < n_active; ++k) {
-    const int64_t id = active_ids[k];
-    const int32_t d = h->dev_of_flow[(size_t)id];
+    const int32_t d = h->dev_of_flow[(size_t)active_ids[k]];
     const int32_t pk = part_of[(size_t)k];
     dev[(size_t)k] = d;
     list[(size_t)(ctl[(size_t)pk].f0 + fill[(size_t)pk]++)] = d;
-    for (int64_t e = h->p_off[(size_t)id]; e < h->p_off[(size_t)id + 1]; ++e)
-      nact[(size_t)h->dev_link[(size_t)scen][(size_t)h->p_link[(size_t)e]]] += 1;
   }
   // exact mode: wide solves on the whole GPU, the others one workgroup each
   std::vector<std::pair<int32_t, int32_t>> wide;
@@ -2190,7 +2183,9 @@ netsim_status netsim_solve_once(netsim_t* h, int32_t scen, int64_t n_active, con
   he = hipMemcpy(P.ctl, ctl.data(), sizeof(ScenCtl) * ctl.size(), hipMemcpyHostToDevice);
   if (he == hipSuccess && h->F > 0)
     he = hipMemcpy(P.act0, list.data(), sizeof(int32_t) * (size_t)h->F, hipMemcpyHostToDevice);
-  if (he == hipSuccess) he = hipMemcpy(P.nact, nact.data(), sizeof(int32_t) * nact.size(), hipMemcpyHostToDevice);
+  if (he == hipSuccess && n_active > 0)
+    he = hipMemcpy(h->d_active, dev.data(), sizeof(int32_t) * (size_t)n_active, hipMemcpyHostToDevice);
+  if (he == hipSuccess) he = netsim_dev::launch_count_active(P, h->d_active, (int)n_active, nullptr);
   if (he != hipSuccess) return hip_fail(h, he, "hipMemcpy (solve_once setup)");
   float ms = 0.0f;
   rc = launch(h, nullptr, true, &ms);
@@ -2221,10 +2216,11 @@ netsim_status netsim_solve_once(netsim_t* h, int32_t scen, int64_t n_active, con
     if (he != hipSuccess) return hip_fail(h, he, "wide exact solve timing");
     ms += gms;
   }
-  std::vector<double> rate((size_t)std::max<int64_t>(h->F, 1));
-  he = hipMemcpy(rate.data(), P.rate, sizeof(double) * (size_t)std::max<int64_t>(h->F, 1), hipMemcpyDeviceToHost);
+  // (through the finish times' place in the results block, unused here)
+  he = netsim_dev::launch_gather_rates(P, h->d_active, (int)n_active, h->res.finish, nullptr);
+  if (he == hipSuccess && n_active > 0)
+    he = hipMemcpy(rates_out, h->res.finish, sizeof(double) * (size_t)n_active, hipMemcpyDeviceToHost);
   if (he != hipSuccess) return hip_fail(h, he, "hipMemcpy (rates)");
-  for (int64_t k = 0; k < n_active; ++k) rates_out[k] = rate[(size_t)dev[(size_t)k]];
   h->stats = netsim_stats{};
   h->stats.complete = 1;
   h->stats.parts = h->num_parts;
@@ -2366,6 +2362,10 @@ void netsim_destroy(netsim_t* h) {
     for (hipEvent_t ev : h->side_ev)
       if (ev) (void)hipEventDestroy(ev);
     if (h->side) (void)hipStreamDestroy(h->side);
+    for (hipEvent_t ev : h->ev)
+      if (ev) (void)hipEventDestroy(ev);
+    if (h->host_pinned) (void)hipHostFree(h->host);
+    else delete[] h->host;
     (void)hipFree(h->d_block);
     if (h->d_hist) (void)hipFree(h->d_hist);
   }
