@@ -149,6 +149,7 @@ struct Params {
   const double* start;     // [F]
   const int32_t* soff;     // [F+1] successor offsets
   const int32_t* succ;     // [nsucc]
+  int2* succ2;             // [F] the first two successors of each flow
   const int64_t* R0;       // [L] capacity in fixed point
   const double* lat;       // [F] path latency (the sum over its links), or NULL: none
   const uint4* path16;     // [F] path as six 16-bit part-local link ids (0xFFFF =
@@ -251,6 +252,8 @@ struct Results {
   double* part_t;
   double* finish;
 };
+// Fills Params::succ2.
+hipError_t launch_succ2(const Params& P, int64_t F, hipStream_t s);
 hipError_t launch_reset(const Params& P, const Initial& I, int64_t F, int64_t L, int NP, hipStream_t s);
 hipError_t launch_reset_words(const Params& P, const Results& R, int scenarios, hipStream_t s);
 hipError_t launch_results(const Params& P, const Results& R, const int32_t* dev_of, const int32_t* scen_of, int64_t F,

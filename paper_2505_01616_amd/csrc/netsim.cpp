@@ -305,10 +305,10 @@ constexpr int32_t kExactGridMin = 16384;
 constexpr int32_t kExactFillMin = 1024;
 constexpr int kGridLevelBatch = 64;
 // Wave kernel: room for active and pending flows at most, and the classes of
-// parts by shared memory (32, 8 or fewer parts on a compute unit at once).
+// parts by shared memory (26, 8 or fewer parts on a compute unit at once).
 constexpr int32_t kWaveSlots = 256, kWavePending = 512;
 constexpr int32_t kXWaveSlots = 512;  // exact mode (its solve's registers hold 8 x 64 flows)
-constexpr size_t kWaveClassBytes[] = {5 * 1024, 20 * 1024, 150 * 1024};
+constexpr size_t kWaveClassBytes[] = {6 * 1024, 20 * 1024, 150 * 1024};
 constexpr int DEBUG_EXACT_GLOBAL = 16;  // options.debug bit 4: exact link state in global memory
 constexpr int DEBUG_EXACT_GRID = 32;  // options.debug bit 5: every such solve on the whole GPU
 
@@ -699,6 +699,7 @@ netsim_status prepare(netsim_t* h) {
       {(void**)&P.unf1, sizeof(int32_t) * Fz},
       {(void**)&P.bar, sizeof(uint32_t) * netsim_dev::BAR_WORDS},
       {(void**)&P.slots, sizeof(uint64_t) * 8},
+      {(void**)&P.succ2, sizeof(int2) * Fz},
       {(void**)&h->init.cnt, sizeof(int32_t) * Fz},
       {(void**)&h->init.rel, sizeof(double) * Fz},
       {(void**)&h->init.pend, sizeof(int32_t) * Fz},
@@ -801,6 +802,9 @@ netsim_status prepare(netsim_t* h) {
     he = hipMemcpy((void*)u.dst, u.src, u.bytes, hipMemcpyHostToDevice);
     if (he != hipSuccess) return hip_fail(h, he, "hipMemcpy (upload)");
   }
+  he = netsim_dev::launch_succ2(P, F, nullptr);
+  if (he == hipSuccess) he = hipStreamSynchronize(nullptr);  // runs use streams of their own
+  if (he != hipSuccess) return hip_fail(h, he, "successor table");
   if (!any_lat) P.lat = nullptr;  // no latency anywhere: arrival = last byte
   if (S == 1) h->d_scen_of = nullptr;
   P.hcount = reinterpret_cast<int32_t*>(P.bar + netsim_dev::BAR_HAND);

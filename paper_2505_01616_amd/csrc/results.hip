@@ -166,6 +166,20 @@ __global__ __launch_bounds__(256) void gather_rates_kernel(Params P, const int32
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) out[i] = P.rate[list[i]];
 }
 
+// Once per handle: the first two successors of every flow, at its own index.
+__global__ __launch_bounds__(256) void succ2_kernel(Params P, int64_t F) {
+  const int64_t f = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (f >= F) return;
+  const int a = P.soff[f], b = P.soff[f + 1];
+  P.succ2[f] = make_int2(a < b ? P.succ[a] : 0, a + 1 < b ? P.succ[a + 1] : 0);
+}
+
+hipError_t launch_succ2(const Params& P, int64_t F, hipStream_t s) {
+  if (F <= 0) return hipSuccess;
+  hipLaunchKernelGGL(succ2_kernel, dim3((unsigned)((F + 255) / 256)), dim3(256), 0, s, P, F);
+  return hipGetLastError();
+}
+
 hipError_t launch_reset(const Params& P, const Initial& I, int64_t F, int64_t L, int NP, hipStream_t s) {
   const int64_t words = (int64_t)NP * (int64_t)(sizeof(ScenCtl) / 8);
   const int64_t most = F > words ? F : words;

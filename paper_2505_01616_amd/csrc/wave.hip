@@ -22,9 +22,9 @@
 //   - a part takes a few kB of shared memory instead of the whole pool, so
 //     a compute unit runs up to 16 parts at once instead of one.
 // Measured (one pass through the C ABI, before: every part in the block kernel):
-// ring all-reduce of 64 GPUs 12.0 -> 5.6 ms (981 events), 3D-parallel step on
-// 128 GPUs 4.7 -> 2.3 ms, training-step trace of 128 GPUs 252 -> 114 ms (22,872
-// events), 33,029 parts of 64 what-if scenarios 5.4 -> 2.8 ms on the device.
+// ring all-reduce of 64 GPUs 12.0 -> 5.4 ms (981 events), 3D-parallel step on
+// 128 GPUs 4.7 -> 1.9 ms, training-step trace of 128 GPUs 252 -> 107 ms (22,872
+// events), 33,029 parts of 64 what-if scenarios 5.4 -> 2.9 ms on the device.
 // A part whose active or pending flows outgrow the shared-memory lists is
 // handed over to the block kernel at that event (its state written out as
 // the event loop's own position, see ScenCtl::mid), which wins once there are
@@ -55,6 +55,7 @@ struct Wave : WaveLog {
   double *tau, *rate, *rem, *tref;  // [sc] slots; a new flow's rate is 0, a free slot's id -1
   uint4* path;     // [sc]
   int32_t *id, *k0, *k1, *comp;     // [sc]
+  int2* s2;        // [sc] first two successors
   uint16_t *sel, *freed;            // [sc] re-solve list (before it: new flows), free slots
   double* prel;    // [pc] pending flows: release time
   int32_t* pid;    // [pc]
@@ -70,7 +71,7 @@ struct Wave : WaveLog {
 
   static __host__ __device__ size_t bytes(int nl, int nc, int sc, int pc) {
     const size_t l = (size_t)((nl + 1 + 7) & ~7), s = (size_t)((sc + 7) & ~7), p = (size_t)((pc + 7) & ~7);
-    return l * 38 + (size_t)nc * 8 + s * 68 + p * 12 + WQ * sizeof(Done) + 32;
+    return l * 38 + (size_t)nc * 8 + s * 76 + p * 12 + WLOG + 32;
   }
 
   __device__ __forceinline__ Wave(const Params& P_, ScenCtl* C_, unsigned char* pool, int sc_, int pc_)
@@ -85,6 +86,8 @@ struct Wave : WaveLog {
     };
     path = reinterpret_cast<uint4*>(take((size_t)s * 16));
     ring = reinterpret_cast<Done*>(take(WQ * sizeof(Done)));
+    next = reinterpret_cast<int2*>(take(64 * sizeof(int2)));
+    s2 = reinterpret_cast<int2*>(take((size_t)s * 8));
     R = reinterpret_cast<int64_t*>(take((size_t)l * 8));
     cap = reinterpret_cast<int64_t*>(take((size_t)l * 8));
     sh = reinterpret_cast<double*>(take((size_t)l * 8));
@@ -123,6 +126,7 @@ struct Wave : WaveLog {
         id[s] = f;
         k0[s] = o.k0;
         k1[s] = o.k1;
+        s2[s] = o.s;
         comp[s] = o.comp - C->c0;
         sel[nArr + r] = (uint16_t)s;
         int lv[6];
@@ -176,7 +180,7 @@ struct Wave : WaveLog {
         P.evd[h] = e;
       }
     }
-    push(zero && o.k1 > o.k0, h, o.k0, o.k1, rl);
+    push(zero && o.k1 > o.k0, h, o.k0, o.k1, o.s, rl);
     activate(act, h, o);
     const uint64_t m = __ballot(later);
     if (m) {
@@ -355,6 +359,7 @@ struct Wave : WaveLog {
       uint4 p{};
       double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
       int x = 0, y = 0, z = 0;
+      int2 v{};
       if (f >= 0) {
         p = path[s];
         a = tau[s];
@@ -364,6 +369,7 @@ struct Wave : WaveLog {
         x = k0[s];
         y = k1[s];
         z = comp[s];
+        v = s2[s];
       }
       wsync();
       const uint64_t m = __ballot(f >= 0);
@@ -378,6 +384,7 @@ struct Wave : WaveLog {
         k0[to] = x;
         k1[to] = y;
         comp[to] = z;
+        s2[to] = v;
       }
       keep += (int)__popcll(m);
       wsync();
@@ -438,6 +445,7 @@ struct Wave : WaveLog {
         id[s] = f;
         k0[s] = o.k0;
         k1[s] = o.k1;
+        s2[s] = o.s;
         comp[s] = o.comp - C->c0;
         const int64_t q = (int64_t)__builtin_rint(r * P.scale);
         int lv[6];
@@ -569,11 +577,13 @@ __device__ __forceinline__ void wave_loop(const Params& P, int part, int sc, int
       const uint64_t m = __ballot(due);
       if (m == 0) continue;
       int f = 0, a = 0, b = 0;
+      int2 next = {0, 0};
       double fin = tn;
       if (due) {
         f = w.id[s];
         a = w.k0[s];
         b = w.k1[s];
+        next = w.s2[s];
         const double r = w.rate[s];
         // the last byte leaves now; it arrives the path latency later
         if (P.lat) fin = tn + P.lat[f];
@@ -599,7 +609,7 @@ __device__ __forceinline__ void wave_loop(const Params& P, int part, int sc, int
         w.tau[s] = WINF;
         w.freed[w.nFree + rank_in(m)] = (uint16_t)s;
       }
-      w.push(due && b > a, f, a, b, fin);
+      w.push(due && b > a, f, a, b, next, fin);
       const int c = (int)__popcll(m);
       w.nFree += c;
       w.ndone += c;
@@ -626,7 +636,7 @@ __device__ __forceinline__ void wave_loop(const Params& P, int part, int sc, int
               P.evd[f] = w.e;
             }
           }
-          w.push(zero && o.k1 > o.k0, f, o.k0, o.k1, rl);
+          w.push(zero && o.k1 > o.k0, f, o.k0, o.k1, o.s, rl);
           w.activate(due && !zero, f, o);
         }
         wsync();
@@ -649,9 +659,9 @@ __device__ __forceinline__ void wave_loop(const Params& P, int part, int sc, int
         // a dependant starts after the latest arrival among its
         // predecessors: every finished flow raises its dependants' base
         // before it counts them down
-        w.successors(cnt, [&](bool in, int k, double fin) {
+        w.successors(cnt, [&](bool in, int g, double fin) {
           if (in)
-            __hip_atomic_fetch_max(reinterpret_cast<uint64_t*>(&P.base[P.succ[k]]),
+            __hip_atomic_fetch_max(reinterpret_cast<uint64_t*>(&P.base[g]),
                                    (uint64_t)__double_as_longlong(fin), __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
         });
@@ -662,7 +672,7 @@ __device__ __forceinline__ void wave_loop(const Params& P, int part, int sc, int
       // entries the countdown appends may reuse the ring slots of this batch
       // (read before the first countdown), never those of later batches that
       // are still in it
-      w.successors(cnt, [&](bool in, int k, double) { w.countdown(in, in ? P.succ[k] : 0); });
+      w.successors(cnt, [&](bool in, int g, double) { w.countdown(in, g); });
       w.qh += cnt;
     }
     wsync();

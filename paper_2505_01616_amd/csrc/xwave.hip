@@ -31,6 +31,7 @@ struct XWave : WaveLog {
   double *rate, *rem, *tau;  // [sc] slots; a free slot's id is -1
   uint4* path;             // [sc] absent links as nl; w: the degree
   int32_t *id, *k0, *k1;   // [sc]
+  int2* s2;                // [sc] first two successors
   uint16_t* freed;         // [sc] free slots
   double* prel;            // [pc] pending flows: release time
   int32_t* pid;            // [pc]
@@ -42,7 +43,7 @@ struct XWave : WaveLog {
 
   static __host__ __device__ size_t bytes(int nl, int sc, int pc) {
     const size_t l = (size_t)((nl + 64 + 7) & ~7), z = (size_t)((sc + 7) & ~7), p = (size_t)((pc + 7) & ~7);
-    return l * 34 + z * 54 + p * 12 + WQ * sizeof(Done) + 32;
+    return l * 34 + z * 62 + p * 12 + WLOG + 32;
   }
 
   __device__ __forceinline__ XWave(const Params& P_, ScenCtl* C_, unsigned char* pool, int sc_, int pc_)
@@ -56,6 +57,8 @@ struct XWave : WaveLog {
     };
     path = reinterpret_cast<uint4*>(take((size_t)z * 16));
     ring = reinterpret_cast<Done*>(take(WQ * sizeof(Done)));
+    next = reinterpret_cast<int2*>(take(64 * sizeof(int2)));
+    s2 = reinterpret_cast<int2*>(take((size_t)z * 8));
     cap = reinterpret_cast<double*>(take((size_t)l * 8));
     R = reinterpret_cast<double*>(take((size_t)l * 8));
     s = reinterpret_cast<double*>(take((size_t)l * 8));
@@ -83,6 +86,7 @@ struct XWave : WaveLog {
     id[at] = f;
     k0[at] = o.k0;
     k1[at] = o.k1;
+    s2[at] = o.s;
   }
 
   // Flow f becomes active (all lanes call it).
@@ -111,7 +115,7 @@ struct XWave : WaveLog {
   __device__ __forceinline__ void arrive(bool in, int f, double rl, const Own& o) {
     const bool later = in && rl > t, zero = in && !later && o.nb == 0.0;
     if (zero) P.finish[f] = rl;
-    push(zero && o.k1 > o.k0, f, o.k0, o.k1, rl);
+    push(zero && o.k1 > o.k0, f, o.k0, o.k1, o.s, rl);
     activate(in && !later && !zero, f, o);
     const uint64_t m = __ballot(later);
     if (m) {
@@ -273,12 +277,14 @@ struct XWave : WaveLog {
       uint4 p{};
       double a = 0.0, b = 0.0;
       int x = 0, y = 0;
+      int2 v{};
       if (f >= 0) {
         p = path[at];
         a = rate[at];
         b = rem[at];
         x = k0[at];
         y = k1[at];
+        v = s2[at];
       }
       wsync();
       const uint64_t m = __ballot(f >= 0);
@@ -290,6 +296,7 @@ struct XWave : WaveLog {
         id[to] = f;
         k0[to] = x;
         k1[to] = y;
+        s2[to] = v;
       }
       keep += (int)__popcll(m);
       wsync();
@@ -414,10 +421,12 @@ __device__ __forceinline__ void xwave_loop(const Params& P, int part, int sc, in
       const int f = at < w.nSlots ? w.id[at] : -1;
       const bool due = f >= 0 && w.tau[at] <= thr;
       int a = 0, b = 0;
+      int2 next = {0, 0};
       double fin = tn;
       if (due) {
         a = w.k0[at];
         b = w.k1[at];
+        next = w.s2[at];
         if (P.lat) fin = tn + P.lat[f];
         P.finish[f] = fin;
         w.id[at] = -1;
@@ -428,7 +437,7 @@ __device__ __forceinline__ void xwave_loop(const Params& P, int part, int sc, in
       const uint64_t m = __ballot(due);
       if (m == 0) continue;
       if (due) w.freed[w.nFree + rank_in(m)] = (uint16_t)at;
-      w.push(due && b > a, f, a, b, fin);
+      w.push(due && b > a, f, a, b, next, fin);
       w.nFree += (int)__popcll(m);
       w.changed = true;
     }
@@ -464,22 +473,20 @@ __device__ __forceinline__ void xwave_loop(const Params& P, int part, int sc, in
     while (w.qh < w.qt) {
       wsync();
       const int cnt = min(64, w.qt - w.qh);
-      w.successors(cnt, [&](bool in, int e, double fin) {
+      w.successors(cnt, [&](bool in, int g, double fin) {
         if (in)
-          __hip_atomic_fetch_max(reinterpret_cast<uint64_t*>(&P.base[P.succ[e]]),
+          __hip_atomic_fetch_max(reinterpret_cast<uint64_t*>(&P.base[g]),
                                  (uint64_t)__double_as_longlong(fin), __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_WORKGROUP);
       });
       // the raises are performed before a base is read
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
       __builtin_amdgcn_s_waitcnt(0);
-      w.successors(cnt, [&](bool in, int e, double) {
-        int g = 0;
+      w.successors(cnt, [&](bool in, int g, double) {
         bool last = false;
         double rl = 0.0;
         Own o{};
         if (in) {
-          g = P.succ[e];
           const int c = __hip_atomic_fetch_add(&P.cnt[g], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           o = own_of(P, g);
           const double st = P.start[g];
