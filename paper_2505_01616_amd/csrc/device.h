@@ -83,7 +83,7 @@ struct ScenCtl {
   int64_t hpos, hbase, hcap, ebase, ecap;
   int64_t launch_events;   // events processed by the last launch
   int32_t status;          // 0 ran to the end, 1 stopped at a limit, < 0 fault
-  int32_t reserved;
+  int32_t deg;             // links of the part's longest path
   int64_t ticks[8];        // wall-clock ticks per phase (first thread of the group)
   int64_t dbg[4];          // debug checks (options.debug)
   Lists k;                 // list counters in global memory (grid layout)

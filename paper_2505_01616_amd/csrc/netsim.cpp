@@ -473,6 +473,7 @@ netsim_status prepare(netsim_t* h) {
     ScenCtl& c = ctl[(size_t)k];
     int32_t deg = 0;
     for (int32_t d = c.f0; d < c.f1; ++d) deg = std::max(deg, poff[(size_t)d + 1] - poff[(size_t)d]);
+    c.deg = deg;
     c.lds_paths = (deg <= 6 && c.l1 - c.l0 < 0xFFFF) ? 1 : 0;
     if (!c.lds_paths) continue;
     for (int32_t d = c.f0; d < c.f1; ++d)

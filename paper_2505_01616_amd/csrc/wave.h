@@ -67,13 +67,15 @@ __device__ __forceinline__ Own own_of(const Params& P, int f) {
   return o;
 }
 
-// Unpacks a path record into part-local link ids; an absent link becomes the
-// sentinel entry nl (share +inf, never stamped).  Returns the degree.
+// Unpacks a path record of at most D links into part-local link ids; an absent
+// link becomes the sentinel entry nl (share +inf, never stamped).  Returns the
+// degree.
+template <int D = 6>
 __device__ __forceinline__ int unpack(const uint4 rec, int nl, int* lv) {
   const uint32_t w[3] = {rec.x, rec.y, rec.z};
   int deg = 0;
 #pragma unroll
-  for (int k = 0; k < 6; ++k) {
+  for (int k = 0; k < D; ++k) {
     const int u = (int)((w[k >> 1] >> (16 * (k & 1))) & 0xFFFFu);
     deg += u != 0xFFFF;
     lv[k] = min(u, nl);

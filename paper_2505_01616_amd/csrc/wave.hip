@@ -22,8 +22,8 @@
 //   - a part takes a few kB of shared memory instead of the whole pool, so
 //     a compute unit runs up to 16 parts at once instead of one.
 // Measured (one pass through the C ABI, before: every part in the block kernel):
-// ring all-reduce of 64 GPUs 12.0 -> 5.4 ms (981 events), 3D-parallel step on
-// 128 GPUs 4.7 -> 1.9 ms, training-step trace of 128 GPUs 252 -> 107 ms (22,872
+// ring all-reduce of 64 GPUs 12.0 -> 4.8 ms (981 events), 3D-parallel step on
+// 128 GPUs 4.7 -> 1.6 ms, training-step trace of 128 GPUs 252 -> 89 ms (22,872
 // events), 33,029 parts of 64 what-if scenarios 5.4 -> 2.9 ms on the device.
 // A part whose active or pending flows outgrow the shared-memory lists is
 // handed over to the block kernel at that event (its state written out as
@@ -39,6 +39,8 @@ namespace {
 
 constexpr double WKEEP = 1.0 - 1e-9;
 
+// D: links of the part's longest path, 2, 4 or 6.
+template <int D>
 struct Wave : WaveLog {
   ScenCtl* C;
   const int nl, sc, pc;
@@ -129,10 +131,10 @@ struct Wave : WaveLog {
         s2[s] = o.s;
         comp[s] = o.comp - C->c0;
         sel[nArr + r] = (uint16_t)s;
-        int lv[6];
-        const int deg = unpack(o.rec, nl, lv);
+        int lv[D];
+        const int deg = unpack<D>(o.rec, nl, lv);
 #pragma unroll
-        for (int k = 0; k < 6; ++k)
+        for (int k = 0; k < D; ++k)
           if (k < deg) ladd(&nact[lv[k]], 1);
       } else {
         P.comp1[f0 + nSpill + (s - sc)] = f;
@@ -207,29 +209,30 @@ struct Wave : WaveLog {
     // flow returned to its links; the first flow of a link lists it
     for (int i0 = 0; i0 < nSel; i0 += 64) {
       const bool in = i0 + lane < nSel;
-      int lv[6], deg = 0;
+      int lv[D], deg = 0;
       if (in) {
         const int s = sel[i0 + lane];
         const double r = rate[s];
-        deg = unpack(path[s], nl, lv);
+        deg = unpack<D>(path[s], nl, lv);
         if (r != 0.0) {
           const double moved = r * (t - tref[s]);
           rem[s] = rem[s] - moved;
           tref[s] = t;
           const int64_t q = (int64_t)__builtin_rint(r * P.scale);
 #pragma unroll
-          for (int k = 0; k < 6; ++k)
+          for (int k = 0; k < D; ++k)
             if (k < deg) ladd(&R[lv[k]], q);
         }
       }
-      int old[6];
+      int old[D];
 #pragma unroll
-      for (int k = 0; k < 6; ++k) {
+      for (int k = 0; k < D; ++k) {
         old[k] = 1;
-        if (in && k < deg) old[k] = __hip_atomic_fetch_add(&n[lv[k]], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (in && k < deg)
+          old[k] = __hip_atomic_fetch_add(&n[lv[k]], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
 #pragma unroll
-      for (int k = 0; k < 6; ++k) {
+      for (int k = 0; k < D; ++k) {
         const bool first = old[k] == 0;
         const uint64_t m = __ballot(first);
         if (first) ll[nt + rank_in(m)] = (uint16_t)lv[k];
@@ -261,24 +264,24 @@ struct Wave : WaveLog {
       bool bad = false;
       double m = 0.0;
       uint32_t cm = 0;
-      int lv[6], deg = 0, s = 0;
+      int lv[D], deg = 0, s = 0;
       bool in = false;
       auto look = [&](int i0) {
         in = i0 + lane < total;
         cm = 0;
         if (!in) return;
         s = sel[i0 + lane];
-        deg = unpack(path[s], nl, lv);
+        deg = unpack<D>(path[s], nl, lv);
         isw += deg;
-        double sv[6];
+        double sv[D];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) sv[k] = sh[lv[k]];
+        for (int k = 0; k < D; ++k) sv[k] = sh[lv[k]];
         m = sv[0];
 #pragma unroll
-        for (int k = 1; k < 6; ++k) m = sv[k] < m ? sv[k] : m;
+        for (int k = 1; k < D; ++k) m = sv[k] < m ? sv[k] : m;
         const double thr = m * WTHR;
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
+        for (int k = 0; k < D; ++k) {
           if (!(sv[k] > thr)) cm |= 1u << k;
           else if (sv[k] < WINF) fl[lv[k]] = st;
         }
@@ -291,14 +294,14 @@ struct Wave : WaveLog {
         bool frozen = false;
         if (in) {
 #pragma unroll
-          for (int k = 0; k < 6; ++k)
+          for (int k = 0; k < D; ++k)
             if ((cm >> k) & 1u) frozen |= fl[lv[k]] != st;
           if (frozen) {
             rate[s] = m;
             tau[s] = t + rem[s] / m;
             const int64_t q = (int64_t)__builtin_rint(m * P.scale);
 #pragma unroll
-            for (int k = 0; k < 6; ++k)
+            for (int k = 0; k < D; ++k)
               if (k < deg) {
                 ladd(&R[lv[k]], -q);
                 ladd(&n[lv[k]], -1);
@@ -332,7 +335,7 @@ struct Wave : WaveLog {
             const uint4 rec = path[s];
             cm = rec.w;
             m = rate[s];
-            deg = unpack(rec, nl, lv);
+            deg = unpack<D>(rec, nl, lv);
           }
           wsync();
           freeze();
@@ -448,10 +451,10 @@ struct Wave : WaveLog {
         s2[s] = o.s;
         comp[s] = o.comp - C->c0;
         const int64_t q = (int64_t)__builtin_rint(r * P.scale);
-        int lv[6];
-        const int deg = unpack(o.rec, nl, lv);
+        int lv[D];
+        const int deg = unpack<D>(o.rec, nl, lv);
 #pragma unroll
-        for (int k = 0; k < 6; ++k)
+        for (int k = 0; k < D; ++k)
           if (k < deg) {
             ladd(&nact[lv[k]], 1);
             ladd(&R[lv[k]], -q);
@@ -507,9 +510,10 @@ struct Wave : WaveLog {
   }
 };
 
+template <int D>
 __device__ __forceinline__ void wave_loop(const Params& P, int part, int sc, int pc, unsigned char* pool) {
   ScenCtl* C = &P.ctl[part];
-  Wave w(P, C, pool, sc, pc);
+  Wave<D> w(P, C, pool, sc, pc);
   const int lane = w.lane;
   const bool resume = P.resume && C->started;
   if (!w.load(resume)) {  // more than the lists hold: the block kernel's from here
@@ -597,10 +601,10 @@ __device__ __forceinline__ void wave_loop(const Params& P, int part, int sc, int
         __hip_atomic_fetch_min(&w.theta[w.comp[s]], (uint64_t)__double_as_longlong(r), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_WORKGROUP);
         const int64_t q = (int64_t)__builtin_rint(r * P.scale);
-        int lv[6];
-        const int deg = unpack(w.path[s], w.nl, lv);
+        int lv[D];
+        const int deg = unpack<D>(w.path[s], w.nl, lv);
 #pragma unroll
-        for (int k = 0; k < 6; ++k)
+        for (int k = 0; k < D; ++k)
           if (k < deg) {
             ladd(&w.nact[lv[k]], -1);
             ladd(&w.R[lv[k]], q);  // its share returns to the link
@@ -688,11 +692,11 @@ __device__ __forceinline__ void wave_loop(const Params& P, int part, int sc, int
       // their links
       for (int i = lane; i < w.nArr; i += 64) {
         const int s = w.sel[i];
-        int lv[6];
-        const int deg = unpack(w.path[s], w.nl, lv);
+        int lv[D];
+        const int deg = unpack<D>(w.path[s], w.nl, lv);
         double lo = WINF;
 #pragma unroll
-        for (int k = 0; k < 6; ++k)
+        for (int k = 0; k < D; ++k)
           if (k < deg) {
             const double s0 = ((double)w.cap[lv[k]] / (double)w.nact[lv[k]]) * P.inv_scale;
             lo = s0 < lo ? s0 : lo;
@@ -805,10 +809,19 @@ __device__ __forceinline__ void wave_loop(const Params& P, int part, int sc, int
 
 __global__ __launch_bounds__(64) void netsim_wave_kernel(Params P, const int32_t* list, int sc, int pc) {
   extern __shared__ __align__(16) unsigned char wpool[];
-  wave_loop(P, list[blockIdx.x], sc, pc, wpool);
+  // a loop over a path's links is unrolled to the longest path of the part:
+  // unpacking and guarding six for paths of one or two was a third of a
+  // solve's instructions (trace of 128 GPUs 106 -> 88 ms, 3D-parallel step 1.95
+  // -> 1.60 ms; one loop that ends on a scalar saved a quarter of that on paths
+  // of two links and cost 15% on longer ones, its reads no longer side by side)
+  const int part = list[blockIdx.x];
+  const int deg = __builtin_amdgcn_readfirstlane(P.ctl[part].deg);
+  if (deg <= 2) wave_loop<2>(P, part, sc, pc, wpool);
+  else if (deg <= 4) wave_loop<4>(P, part, sc, pc, wpool);
+  else wave_loop<6>(P, part, sc, pc, wpool);
 }
 
-size_t wave_bytes(int nl, int nc, int sc, int pc) { return Wave::bytes(nl, nc, sc, pc); }
+size_t wave_bytes(int nl, int nc, int sc, int pc) { return Wave<6>::bytes(nl, nc, sc, pc); }
 
 hipError_t launch_wave(const Params& p, const int32_t* list, int parts, int sc, int pc, size_t lds, hipStream_t s) {
   hipError_t e = hipFuncSetAttribute((const void*)netsim_wave_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,

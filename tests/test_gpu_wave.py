@@ -32,7 +32,7 @@ def _say(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def _release(n, lagged, latency=False, links=40, seed=9):
+def _release(n, lagged, latency=False, links=40, seed=9, deg=6):
     """A flow, then n flows released by its end (all at once, or each at an
     instant of its own), then a barrier over them and 150 zero-byte flows
     that finish together, each with a flow after it."""
@@ -46,7 +46,7 @@ def _release(n, lagged, latency=False, links=40, seed=9):
     ids = []
     for i in range(n):
         r = u[100 + 8 * i:108 + 8 * i]
-        path = sorted({int(x * links) for x in r[:1 + int(6 * r[6])]})
+        path = sorted({int(x * links) for x in r[:1 + int(deg * r[6])]})
         ids.append(sc.add(PathFlow(path, float(1 + int(40 * r[7])), lag=float(1.0 + 7.0 * r[5]) if lagged else 0.0,
                                    after=(first,))))
     b = sc.add(Barrier(after=tuple(ids)))
@@ -97,6 +97,23 @@ def test_exact_hand_over(n, lagged, latency):
         assert np.array_equal(ns.netsim_get_finish(ld.handle), want.finish)
     finally:
         ld.close()
+
+
+@pytest.mark.parametrize("deg", [1, 2, 3, 4, 5, 6, 7])
+def test_path_lengths(deg):
+    """The longest path chooses the loop (2, 4 or 6 links; longer: the workgroup kernel)."""
+    ns, pr = _gpu()
+    program = _release(120, False, True, links=60, deg=deg)
+    paths = [f.path for f in program.scenarios[0].ops if isinstance(f, PathFlow)]
+    _say(f"test_path_lengths deg={deg} longest={max(map(len, paths))}")
+    assert max(map(len, paths)) == deg
+    a, sa = pr.run_program(program, ns.make_options())
+    b, sb = pr.run_program(program, ns.make_options(block_threads=512))
+    assert np.array_equal(a[0], b[0])
+    for k in SAME:
+        assert sa[k] == sb[k], (k, sa[k], sb[k])
+    want = osim.run_scenario(program.scenarios[0]).finish
+    assert np.max(np.abs(a[0] - want) / want) < 1e-9
 
 
 @pytest.mark.parametrize("history", [0, 8])
