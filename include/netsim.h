@@ -63,7 +63,8 @@ enum {
                             predecessors; cluster with at most 4 parts per XCD
                             and a part with > 16384 of them; else block        */
   NETSIM_EXEC_GRID = 1,  /* whole GPU on one part at a time (grid barriers)      */
-  NETSIM_EXEC_BLOCK = 2,  /* one workgroup per part (workgroup barriers)         */
+  NETSIM_EXEC_BLOCK = 2,  /* one wavefront per small part, one workgroup per other
+                             part (workgroup barriers)                           */
   NETSIM_EXEC_CLUSTER = 3, /* leader workgroups (one per XCD, or up to 4 per XCD
                              when there are more parts than XCDs) run parts as
                              in block mode and hand re-solves of at least
@@ -73,8 +74,9 @@ enum {
                              bit for bit.  Rate solves without an
                              event loop (netsim_solve_once) run as in block mode */
   NETSIM_EXEC_EXACT = 4   /* reported in netsim_stats.layout when
-                             netsim_options.exact is set (one workgroup per
-                             scenario, the exact-arithmetic kernel)            */
+                             netsim_options.exact is set (one wavefront or
+                             workgroup per scenario, the exact-arithmetic
+                             kernels)                                            */
 };
 
 /*
@@ -93,9 +95,12 @@ typedef struct {
   int64_t max_events;        /* stop each part after this many events; 0 = no limit */
   double until;              /* do not process events later than this time (s); +inf = none */
   int32_t max_rounds;        /* per-solve round watchdog; 0 = number of flows + 1 */
-  int32_t block_threads;     /* threads per workgroup in block mode; 0 = 1024 if
-                                a part has > 16384 flows without predecessors,
-                                else 512                                        */
+  int32_t block_threads;     /* threads per workgroup in block and exact mode,
+                                every part in a workgroup of its own; 0 = small
+                                parts one wavefront each, the others 1024 threads
+                                if a part has > 16384 flows without predecessors,
+                                else 512 (exact mode: 512); the results are the
+                                same bit for bit                                */
   int32_t debug;             /* bit 0: consistency checks on the device; bit 1:
                                 phase timers (netsim_stats.phase_seconds); test
                                 hooks of NETSIM_EXEC_CLUSTER: bit 2 makes helper
@@ -104,7 +109,8 @@ typedef struct {
                                 barrier give up at once (the run then fails with
                                 NETSIM_E_DEVICE, "grid barrier timed out"); bit
                                 4 keeps exact-mode link state in global memory
-                                even where it fits shared memory; bit 5 runs
+                                even where it fits shared memory (every scenario
+                                in a workgroup of its own); bit 5 runs
                                 every exact-mode solve_once on the whole GPU;
                                 bit 6 makes every release of NETSIM_EXEC_CLUSTER
                                 an agent-scope release fence (slower; results
@@ -126,8 +132,8 @@ typedef struct {
                                 difference), n_l -= k_l; every active flow's
                                 remaining bytes drop by rate*(t_next - t) at
                                 every event; a flow finishes when
-                                t + rem/rate <= t_next(1 + 1e-12).  One workgroup
-                                per scenario (exec, assist_* ignored; stats.layout
+                                t + rem/rate <= t_next(1 + 1e-12).  One wavefront
+                                or workgroup per scenario (exec, assist_* ignored; stats.layout
                                 = NETSIM_EXEC_EXACT).  Finish times are the same
                                 bit for bit for any workgroup size.  0: the
                                 default solver (local-minimum rounds, int64
@@ -226,7 +232,8 @@ typedef struct {
    * [0] next-event search, [1] settling completions and releases, [2] solve
    * set-up and the share table of every round, [3] share/blocking sweep, [4]
    * wait after it, [5] freezing sweep, [6] wait after it, [7] choosing the
-   * flows to re-solve.  In the cluster layout a re-solve run by helper
+   * flows to re-solve.  Parts run by one wavefront count their whole solve in
+   * [3].  In the cluster layout a re-solve run by helper
    * workgroups counts with the first helper's times in [2]-[6]; the hand-over
    * itself (copying link state, waking the helpers) is not counted. */
   double phase_seconds[8];
