@@ -252,9 +252,8 @@ struct Results {
   double* part_t;
   double* finish;
 };
-// Fills Params::succ2.
-hipError_t launch_succ2(const Params& P, int64_t F, hipStream_t s);
-hipError_t launch_reset(const Params& P, const Initial& I, int64_t F, int64_t L, int NP, hipStream_t s);
+// (first: fills Params::succ2 too)
+hipError_t launch_reset(const Params& P, const Initial& I, int64_t F, int64_t L, int NP, bool first, hipStream_t s);
 hipError_t launch_reset_words(const Params& P, const Results& R, int scenarios, hipStream_t s);
 hipError_t launch_results(const Params& P, const Results& R, const int32_t* dev_of, const int32_t* scen_of, int64_t F,
                           hipStream_t s);

@@ -1,6 +1,7 @@
 // Exact progressive filling on gfx950: the event loop and rate solve of the
 // fluid model carried out with the arithmetic of a sequential fp64 program,
-// one workgroup per scenario (batched scenarios run side by side).
+// one workgroup per scenario (batched scenarios run side by side; small ones
+// take one wavefront instead, xwave.hip).
 //
 // Model (Section 4.1, netsim; Section 4.2, the network simulator with time
 // rollback): active flows share link bandwidth max-min fairly (per-flow

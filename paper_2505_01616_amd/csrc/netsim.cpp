@@ -4,9 +4,9 @@
 // decomposition of ring and all-to-all collectives into flows (Section 4.1:
 // collectives as communication patterns, all-reduce as NCCL's ring), the
 // device layout (flows grouped by scenario, links compacted to the used
-// ones, successor lists, fixed-point capacities), upload, one kernel launch
-// per run, and results.  Every step of the simulation itself runs in the
-// HIP kernels (kernels.hip).
+// ones, successor lists, fixed-point capacities), upload, a run's kernel
+// launches, and one copy of the results.  Every step of the simulation itself
+// runs in the HIP kernels (kernels.hip, wave.hip; exact mode exact.hip, xwave.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -108,6 +108,7 @@ struct netsim {
   int32_t* d_dev_of = nullptr;        // id -> device flow
   int32_t* d_active = nullptr;        // device flows of a single rate solve
   int32_t* d_scen_of = nullptr;       // id -> scenario (NULL: one scenario)
+  bool succ2_done = false;            // Params::succ2 filled (by the first reset)
   int64_t widest = 0;                 // flows without predecessors in the widest part
   hipEvent_t ev[2] = {};              // around a launch
   const char* at_host(const void* dev) const { return host + ((const char*)dev - (const char*)res.totals); }
@@ -304,6 +305,7 @@ constexpr int kExactThreads = 512;
 constexpr int32_t kExactGridMin = 16384;
 constexpr int32_t kExactFillMin = 1024;
 constexpr int kGridLevelBatch = 64;
+constexpr size_t kPinnedMin = 256 * 1024;  // results at least this long are copied to pinned memory
 // Wave kernel: room for active and pending flows at most, and the classes of
 // parts by shared memory (26, 8 or fewer parts on a compute unit at once).
 constexpr int32_t kWaveSlots = 256, kWavePending = 512;
@@ -745,9 +747,11 @@ netsim_status prepare(netsim_t* h) {
   h->res.makespan = (uint64_t*)(h->res.totals + 1);
   h->res.part_t = (double*)(h->res.makespan + S);
   h->res.finish = h->res.part_t + NP;
-  if (hipHostMalloc((void**)&h->host, h->res_bytes, hipHostMallocDefault) == hipSuccess) {
-    h->host_pinned = true;
-  } else {
+  // (small results come through pageable memory: getting and giving back pinned
+  // memory costs a handle more than its copies save)
+  h->host_pinned = h->res_bytes >= kPinnedMin &&
+                   hipHostMalloc((void**)&h->host, h->res_bytes, hipHostMallocDefault) == hipSuccess;
+  if (!h->host_pinned) {
     (void)hipGetLastError();
     h->host = new (std::nothrow) char[h->res_bytes];
     if (!h->host) return fail(h, NETSIM_E_NOMEM, "no host memory for the results");
@@ -803,9 +807,6 @@ netsim_status prepare(netsim_t* h) {
     he = hipMemcpy((void*)u.dst, u.src, u.bytes, hipMemcpyHostToDevice);
     if (he != hipSuccess) return hip_fail(h, he, "hipMemcpy (upload)");
   }
-  he = netsim_dev::launch_succ2(P, F, nullptr);
-  if (he == hipSuccess) he = hipStreamSynchronize(nullptr);  // runs use streams of their own
-  if (he != hipSuccess) return hip_fail(h, he, "successor table");
   if (!any_lat) P.lat = nullptr;  // no latency anywhere: arrival = last byte
   if (S == 1) h->d_scen_of = nullptr;
   P.hcount = reinterpret_cast<int32_t*>(P.bar + netsim_dev::BAR_HAND);
@@ -819,7 +820,8 @@ netsim_status prepare(netsim_t* h) {
 // Resets the dynamic state for a run from t = 0 (on `stream`, in its order).
 netsim_status reset_state(netsim_t* h, hipStream_t st) {
   h->hist_ok = h->prm.hist != nullptr;
-  const hipError_t he = netsim_dev::launch_reset(h->prm, h->init, h->F, h->L, h->num_parts, st);
+  const hipError_t he = netsim_dev::launch_reset(h->prm, h->init, h->F, h->L, h->num_parts, !h->succ2_done, st);
+  h->succ2_done = h->succ2_done || he == hipSuccess;
   return he == hipSuccess ? NETSIM_OK : hip_fail(h, he, "reset of the state");
 }
 
@@ -864,7 +866,7 @@ hipError_t launch_event_loops(netsim_t* h, const Params& P0, hipStream_t st, con
   return he;
 }
 
-// One kernel launch: a rate solve per part (solve_only), or the event loop of
+// One sequence of launches: a rate solve per part (solve_only), or the event loop of
 // every part from t = 0 or, with resume, from where the last launch stopped,
 // processing events up to `until` and at most max_events more per part.
 netsim_status launch(netsim_t* h, hipStream_t st, bool solve_only, float* ms, bool resume = false,
@@ -2279,6 +2281,8 @@ netsim_status netsim_bench_sweeps(netsim_t* h, int32_t scen, int64_t n_active, c
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   rc = reset_state(h, st);
   if (rc) return rc;
+  he = hipStreamSynchronize(st);
+  if (he != hipSuccess) return hip_fail(h, he, "hipStreamSynchronize (reset)");
   int32_t p = -1;  // exact mode: one part per scenario
   for (int32_t k = 0; k < h->num_parts; ++k)
     if (h->h_ctl0[(size_t)k].scen == scen) p = k;

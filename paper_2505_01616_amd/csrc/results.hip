@@ -35,7 +35,8 @@ __device__ __forceinline__ uint64_t max_wave(uint64_t v) {
 
 }  // namespace
 
-__global__ __launch_bounds__(256) void reset_state_kernel(Params P, Initial I, int64_t F, int64_t L, int64_t ctl_words) {
+__global__ __launch_bounds__(256) void reset_state_kernel(Params P, Initial I, int64_t F, int64_t L, int64_t ctl_words,
+                                                          bool first) {
   const int64_t n = (int64_t)gridDim.x * blockDim.x, i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const double nan = __longlong_as_double(0x7FF8000000000000ll);
   for (int64_t i = i0; i < F; i += n) {
@@ -46,6 +47,11 @@ __global__ __launch_bounds__(256) void reset_state_kernel(Params P, Initial I, i
     P.base[i] = 0.0;
     P.rate[i] = 0.0;
   }
+  if (first)  // a handle's first reset: the first two successors of every flow, at its own index
+    for (int64_t i = i0; i < F; i += n) {
+      const int a = P.soff[i], b = P.soff[i + 1];
+      P.succ2[i] = make_int2(a < b ? P.succ[a] : 0, a + 1 < b ? P.succ[a + 1] : 0);
+    }
   if (P.hist)
     for (int64_t i = i0; i < F; i += n) {
       P.evr[i] = EV_NEVER;
@@ -166,25 +172,11 @@ __global__ __launch_bounds__(256) void gather_rates_kernel(Params P, const int32
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) out[i] = P.rate[list[i]];
 }
 
-// Once per handle: the first two successors of every flow, at its own index.
-__global__ __launch_bounds__(256) void succ2_kernel(Params P, int64_t F) {
-  const int64_t f = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (f >= F) return;
-  const int a = P.soff[f], b = P.soff[f + 1];
-  P.succ2[f] = make_int2(a < b ? P.succ[a] : 0, a + 1 < b ? P.succ[a + 1] : 0);
-}
-
-hipError_t launch_succ2(const Params& P, int64_t F, hipStream_t s) {
-  if (F <= 0) return hipSuccess;
-  hipLaunchKernelGGL(succ2_kernel, dim3((unsigned)((F + 255) / 256)), dim3(256), 0, s, P, F);
-  return hipGetLastError();
-}
-
-hipError_t launch_reset(const Params& P, const Initial& I, int64_t F, int64_t L, int NP, hipStream_t s) {
+hipError_t launch_reset(const Params& P, const Initial& I, int64_t F, int64_t L, int NP, bool first, hipStream_t s) {
   const int64_t words = (int64_t)NP * (int64_t)(sizeof(ScenCtl) / 8);
   const int64_t most = F > words ? F : words;
   const int blocks = (int)((most + 1023) / 1024 < 1 ? 1 : (most + 1023) / 1024 > 2048 ? 2048 : (most + 1023) / 1024);
-  hipLaunchKernelGGL(reset_state_kernel, dim3(blocks), dim3(256), 0, s, P, I, F, L, words);
+  hipLaunchKernelGGL(reset_state_kernel, dim3(blocks), dim3(256), 0, s, P, I, F, L, words, first);
   return hipGetLastError();
 }
 
