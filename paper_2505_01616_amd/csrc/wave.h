@@ -130,7 +130,7 @@ struct WaveLog {
         a = P.soff[f];
         b = P.soff[f + 1];
         s = P.succ2[f];
-        if (P.lat) fin = P.finish[f];
+        fin = P.finish[f];  // (the flow's event stored it before it logged the flow)
       }
     }
     const uint64_t wide = __ballot(b - a > 8);

@@ -145,3 +145,55 @@ def test_pieces_and_rollback(n, lagged, history):
         assert np.array_equal(ns.netsim_get_finish(ld.handle), want2[0])
     finally:
         ld.close()
+
+
+def _followed(n, latency):
+    """n flows and 90 zero-byte flows that end at one instant, each followed by
+    a computation, a second one after it and a lagged flow after that, and by
+    a lagged flow of its own: every release lies after its predecessor's end
+    by a lag of its own."""
+    topo = Topology(kind="explicit", capacities=np.full(n, 2.0))
+    if latency:
+        topo.latencies = 0.25 + 0.125 * (np.arange(n) % 5)
+    sc = Scenario(topo)
+    first = sc.add(PathFlow([0], 2.0))
+    ends = [sc.add(PathFlow([i], 20.0, after=(first,))) for i in range(n)]
+    at = sc.add(Barrier(lag=64.0, after=(first,)))
+    ends += [sc.add(Barrier(after=(at,))) for _ in range(90)]
+    for i, f in enumerate(ends):
+        c = sc.add(Barrier(lag=0.001 * (1 + i), after=(f,)))
+        d = sc.add(Barrier(lag=0.5, after=(c,)))
+        sc.add(PathFlow([i % n], 3.0, lag=0.25, after=(d,)))
+        sc.add(PathFlow([i % n], 2.0 + i % 7, lag=1.0 + 0.125 * (i % 5), after=(f,)))
+    return Program(f"followed-{n}", [sc])
+
+
+@pytest.mark.parametrize("latency", [False, True])
+@pytest.mark.parametrize("n", [64, 65, 128, 200])
+def test_many_ends_followed_by_lags(n, latency):
+    """More flows end in one event than the newest 64 that the log keeps in
+    shared memory, and everything after them counts from their ends: exact
+    mode bit for bit the oracle, whole and in pieces; the default solver bit
+    for bit the workgroup kernel's."""
+    ns, pr = _gpu()
+    program = _followed(n, latency)
+    _say(f"test_many_ends_followed_by_lags n={n} latency={latency}")
+    want = osim.run_scenario(program.scenarios[0])
+    a, sa = pr.run_program(program, ns.make_options(exact=1))
+    assert np.array_equal(a[0], want.finish)
+    assert (sa["events"], sa["solves"], sa["rounds"]) == (want.events, want.solves, want.iterations)
+    ld = pr.load_program(program, ns.make_options(exact=1))
+    try:
+        for _ in range(400):
+            ns.netsim_advance(ld.handle, max_events=13)
+            if ns.netsim_get_stats(ld.handle)["complete"]:
+                break
+        assert np.array_equal(ns.netsim_get_finish(ld.handle), want.finish)
+    finally:
+        ld.close()
+    b, sb = pr.run_program(program, ns.make_options())
+    c, sc = pr.run_program(program, ns.make_options(block_threads=512))
+    assert np.array_equal(b[0], c[0])
+    for k in SAME:
+        assert sb[k] == sc[k], (k, sb[k], sc[k])
+    assert np.max(np.abs(b[0] - want.finish) / want.finish) < 1e-9
