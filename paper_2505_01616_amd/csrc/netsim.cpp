@@ -2034,6 +2034,11 @@ netsim_status netsim_update_start(netsim_t* h, int64_t id, double start) {
   const Params& P = h->prm;
   const int32_t d = h->dev_of_flow[(size_t)id];
   he = hipMemcpy(const_cast<double*>(P.start) + d, &start, sizeof(double), hipMemcpyHostToDevice);
+  if (he == hipSuccess && h->h_cnt0[(size_t)d] == 0) {
+    // its release in the state at t = 0, which runs and rollbacks start from
+    he = hipMemcpy(const_cast<double*>(h->init.rel) + d, &start, sizeof(double), hipMemcpyHostToDevice);
+    if (he == hipSuccess) h->h_rel0[(size_t)d] = start;
+  }
   if (he != hipSuccess) return hip_fail(h, he, "hipMemcpy (start)");
   if (!h->has_state) return NETSIM_OK;  // the next run starts from t = 0 with it
   const int32_t p = part_of_dev(h, d);

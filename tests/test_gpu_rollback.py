@@ -15,6 +15,7 @@ import pytest
 
 from oracle import flows as oflows
 from oracle import sim as osim
+from tests.helpers import explicit
 from workloads import configs, micro
 from workloads.program import Program
 
@@ -378,3 +379,63 @@ def test_history_rollback_random_micro_batch():
         ref = _oracle(sc, {loc: v for (t, loc), v in upd.items() if t == s})
         assert _rel(got[a:a + ld.num_flows[s]], ref) < TOL, s
     assert not np.array_equal(got, base)
+
+
+def _timed_starts():
+    """One link; flows without predecessors at 0, 3 and 5 s, and one 6 s after
+    the first of them ends."""
+    return Program("starts", [explicit([10.0], [
+        {"path": [0], "nbytes": 10.0}, {"path": [0], "nbytes": 20.0, "lag": 3.0},
+        {"path": [0], "nbytes": 30.0, "lag": 5.0}, {"path": [0], "nbytes": 5.0, "lag": 6.0, "after": [0]}])])
+
+
+MODES = [dict(), dict(block_threads=512), dict(exact=1), dict(history_mb=4)]
+
+
+@pytest.mark.parametrize("opt", MODES)
+def test_updated_start_without_predecessors_in_the_next_run(opt):
+    """A start changed after the handle was prepared (by a run, or by a rate
+    solve) is the one that a run from t = 0 uses."""
+    ns, pr = _gpu()
+    _say(f"test_updated_start_next_run {opt}")
+    program = _timed_starts()
+    upd = {0: 1.5, 2: 0.25}
+    want = _fresh(program, upd, **opt)
+    assert _rel(want, _oracle(program.scenarios[0], upd)) < TOL
+    for solve_first in (False, True):
+        ld = pr.load_program(program, ns.make_options(**opt))
+        try:
+            if solve_first:
+                ns.netsim_solve_once(ld.handle, 0, np.arange(4))
+            else:
+                ns.netsim_run(ld.handle)
+            for fid, st in upd.items():
+                ns.netsim_update_start(ld.handle, fid, st)
+            for _ in range(2):
+                ns.netsim_run(ld.handle)
+                assert np.array_equal(ns.netsim_get_finish(ld.handle), want)
+        finally:
+            ld.close()
+
+
+@pytest.mark.parametrize("opt", MODES)
+def test_updates_before_a_rollback_to_the_start(opt):
+    """Starts changed one after another, the later changes returning the part
+    to t = 0: the earlier ones hold."""
+    ns, pr = _gpu()
+    _say(f"test_updates_rollback_to_start {opt}")
+    program = _timed_starts()
+    upd = {}
+    ld = pr.load_program(program, ns.make_options(**opt))
+    try:
+        ns.netsim_advance(ld.handle, until=6.0)
+        for fid, st in ((2, 4.0), (1, 2.5), (0, 1.0)):
+            upd[fid] = st
+            ns.netsim_update_start(ld.handle, fid, st)
+            ns.netsim_advance(ld.handle, until=6.0)
+        ns.netsim_advance(ld.handle)
+        got = ns.netsim_get_finish(ld.handle)
+    finally:
+        ld.close()
+    assert np.array_equal(got, _fresh(program, upd, **opt))
+    assert _rel(got, _oracle(program.scenarios[0], upd)) < TOL
