@@ -254,6 +254,8 @@ struct Results {
 };
 // (first: fills Params::succ2 too)
 hipError_t launch_reset(const Params& P, const Initial& I, int64_t F, int64_t L, int NP, bool first, hipStream_t s);
+// Releases of the flows [f0, f1) without a predecessor left, from their present starts.
+hipError_t launch_releases(const Params& P, int f0, int f1, hipStream_t s);
 hipError_t launch_reset_words(const Params& P, const Results& R, int scenarios, hipStream_t s);
 hipError_t launch_results(const Params& P, const Results& R, const int32_t* dev_of, const int32_t* scen_of, int64_t F,
                           hipStream_t s);

@@ -1236,6 +1236,8 @@ netsim_status restore_part(netsim_t* h, int32_t p, int k) {
     }
     const size_t coff = (size_t)((char*)P.ctl - h->persist) + sizeof(ScenCtl) * (size_t)p;
     if (he == hipSuccess) he = hipMemcpy(P.ctl + p, src + coff, sizeof(ScenCtl), hipMemcpyDeviceToDevice);
+    // starts may have changed since the checkpoint was kept
+    if (he == hipSuccess) he = netsim_dev::launch_releases(P, c0.f0, c0.f1, nullptr);
   } else {
     std::vector<double> nan(n, std::numeric_limits<double>::quiet_NaN()), zero(n, 0.0);
     if (n > 0) {

@@ -65,6 +65,14 @@ __global__ __launch_bounds__(256) void reset_state_kernel(Params P, Initial I, i
   for (int64_t i = i0; i < ctl_words; i += n) dst[i] = src[i];
 }
 
+// Releases of the flows [f0, f1) that no predecessor holds back, from their
+// present starts (after a rollback to a checkpoint: a flow still pending there
+// may have got another start since; the others get the value they had).
+__global__ __launch_bounds__(256) void releases_kernel(Params P, int f0, int f1) {
+  const int f = f0 + (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (f < f1 && P.cnt[f] == 0) P.rel[f] = P.start[f] + P.base[f];
+}
+
 // Synchronisation words, reduction slots and totals of a launch.
 __global__ __launch_bounds__(256) void reset_launch_kernel(Params P, Results R, int num_scen_out) {
   const int n = gridDim.x * blockDim.x, i0 = blockIdx.x * blockDim.x + threadIdx.x;
@@ -177,6 +185,12 @@ hipError_t launch_reset(const Params& P, const Initial& I, int64_t F, int64_t L,
   const int64_t most = F > words ? F : words;
   const int blocks = (int)((most + 1023) / 1024 < 1 ? 1 : (most + 1023) / 1024 > 2048 ? 2048 : (most + 1023) / 1024);
   hipLaunchKernelGGL(reset_state_kernel, dim3(blocks), dim3(256), 0, s, P, I, F, L, words, first);
+  return hipGetLastError();
+}
+
+hipError_t launch_releases(const Params& P, int f0, int f1, hipStream_t s) {
+  if (f1 <= f0) return hipSuccess;
+  hipLaunchKernelGGL(releases_kernel, dim3((unsigned)((f1 - f0 + 255) / 256)), dim3(256), 0, s, P, f0, f1);
   return hipGetLastError();
 }
 

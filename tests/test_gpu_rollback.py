@@ -439,3 +439,27 @@ def test_updates_before_a_rollback_to_the_start(opt):
         ld.close()
     assert np.array_equal(got, _fresh(program, upd, **opt))
     assert _rel(got, _oracle(program.scenarios[0], upd)) < TOL
+
+
+@pytest.mark.parametrize("opt", MODES)
+def test_update_of_pending_flows_before_a_rollback_to_a_checkpoint(opt):
+    """Pending flows (one without predecessors, one whose predecessor has
+    ended) get later starts after a checkpoint was kept; a rollback to it for
+    another flow does not bring their old releases back."""
+    ns, pr = _gpu()
+    _say(f"test_update_pending_checkpoint {opt}")
+    program = _timed_starts()
+    upd = {2: 7.0, 3: 8.0, 1: 2.0}
+    ld = pr.load_program(program, ns.make_options(**opt))
+    try:
+        ns.netsim_advance(ld.handle, until=1.5)
+        for fid in (2, 3):
+            ns.netsim_update_start(ld.handle, fid, upd[fid])
+        ns.netsim_advance(ld.handle, until=9.5)
+        ns.netsim_update_start(ld.handle, 1, upd[1])
+        ns.netsim_advance(ld.handle)
+        got = ns.netsim_get_finish(ld.handle)
+    finally:
+        ld.close()
+    assert np.array_equal(got, _fresh(program, upd, **opt))
+    assert _rel(got, _oracle(program.scenarios[0], upd)) < TOL
