@@ -50,25 +50,12 @@ __device__ __forceinline__ double wave_min(double v) {
   return v;
 }
 
-// A value every lane of the wave holds, kept in scalar registers (values
-// read from shared memory would otherwise occupy vector registers, and the
-// branches on them lane masks).
-__device__ __forceinline__ int scalar(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ uint32_t scalar(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-__device__ __forceinline__ int64_t scalar(int64_t v) {
-  return (int64_t)(((uint64_t)scalar((uint32_t)(v >> 32)) << 32) | scalar((uint32_t)v));
-}
-__device__ __forceinline__ double scalar(double v) {
-  return __longlong_as_double((long long)scalar((int64_t)__double_as_longlong(v)));
-}
-
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 
 // ------------------------------------------------------------------ groups
-// TIGHT: the cluster kernel's leader (see fresh()).  MID: the event loop
-// may start in the middle of an event (parts handed over by the wave kernel;
-// the 512-thread kernel takes them).
-template <bool TIGHT, bool MID>
+// MID: the event loop may start in the middle of an event (parts handed over
+// by the wave kernel; the 512-thread kernel takes them).
+template <bool MID>
 struct BlockG {
   static constexpr bool kMid = MID;
   double* lds;
@@ -76,24 +63,8 @@ struct BlockG {
   Lists* lst;  // list counters: shared memory (block kernel, zeroed when a part
                // starts) or the part's control block (a solve run by one workgroup
                // of the grid)
-  int t = (int)threadIdx.x;
-  // The thread index as a value the compiler cannot see through: addresses
-  // are computed again after it.  Hoisted out of the event loop they take
-  // more registers than the cluster kernel has (128 per lane; 186 spilled, 76
-  // with this and scalar loop state: 7% of the time of an all-to-all of 448
-  // GPUs); a 512-thread build has room for them and is 2% faster with them.
-  __device__ __forceinline__ void fresh() {
-    if constexpr (TIGHT) asm volatile("" : "+v"(t));
-  }
-  // Loop state in scalar registers: the 512-thread build has vector
-  // registers to spare for it, but scalar ones already spill there.
-  template <class T>
-  __device__ __forceinline__ T uni(T v) const {
-    if constexpr (TIGHT) return scalar(v);
-    else return v;
-  }
   __device__ Lists* lists(ScenCtl*) const { return lst; }
-  __device__ int tid() const { return t; }
+  __device__ int tid() const { return threadIdx.x; }
   __device__ int block_base() const { return 0; }
   __device__ int nblocks() const { return 1; }
   __device__ int block_id() const { return 0; }
@@ -154,8 +125,6 @@ struct GridG {
   uint32_t nred;
   bool ab;        // block-uniform copy of *flag, refreshed at every barrier
   uint32_t xcc, mine, nx;  // this block's XCD, blocks on it, XCDs in use
-  template <class T>
-  __device__ __forceinline__ T uni(T v) const { return v; }
   __device__ int tid() const { return blockIdx.x * blockDim.x + threadIdx.x; }
   __device__ int block_base() const { return blockIdx.x * blockDim.x; }
   __device__ int nblocks() const { return gridDim.x; }
@@ -483,11 +452,6 @@ struct ClusterG {
   }
 };
 
-template <class G>
-__device__ __forceinline__ int local_id(const G&) { return (int)threadIdx.x; }
-template <bool TIGHT, bool MID>
-__device__ __forceinline__ int local_id(const BlockG<TIGHT, MID>& g) { return g.t; }
-
 template <class G> struct IsGrid { static constexpr bool value = false; };
 template <> struct IsGrid<GridG> { static constexpr bool value = true; };
 template <class G> struct IsCluster { static constexpr bool value = false; };
@@ -561,12 +525,12 @@ __device__ __forceinline__ void sweep_append(G& g, int n, int32_t* const* counte
       Item x[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int i = local_id(g) + (j0 + u) * T;
+        const int i = (int)threadIdx.x + (j0 + u) * T;
         if (i < n) x[u] = fetch(i);
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int i = local_id(g) + (j0 + u) * T;
+        const int i = (int)threadIdx.x + (j0 + u) * T;
         bool pr[NL] = {};
         if (i < n) decide(i, x[u], pr);
 #pragma unroll
@@ -997,7 +961,8 @@ __device__ __forceinline__ double rem_at(double rem, double r, double t, double 
 }
 
 // Bit k set for every item t + k*T < n of this thread (k < 64).
-__device__ __forceinline__ uint64_t low_items(int n, int T, int t) {
+__device__ __forceinline__ uint64_t low_items(int n, int T) {
+  const int t = threadIdx.x;
   const int c = n > t ? (n - t - 1) / T + 1 : 0;
   return c >= 64 ? ~0ull : (1ull << c) - 1ull;
 }
@@ -1010,7 +975,7 @@ __device__ __forceinline__ uint64_t low_items(int n, int T, int t) {
 // read are never merged into one access through a generic pointer.
 template <class Body>
 __device__ __forceinline__ void for_items(uint64_t mask, uint64_t cmask, const FlowCache& fc,
-                                          const uint4* stg, int T, int t, Body body) {
+                                          const uint4* stg, int T, Body body) {
   for (uint64_t m = mask & cmask; m;) {
     int k[4];
     uint4 r[4];
@@ -1018,11 +983,11 @@ __device__ __forceinline__ void for_items(uint64_t mask, uint64_t cmask, const F
     for (int u = 0; u < 4; ++u) {
       k[u] = m ? __ffsll((unsigned long long)m) - 1 : -1;
       m &= m - 1;
-      if (k[u] >= 0) r[u] = fc.path[t + k[u] * T];
+      if (k[u] >= 0) r[u] = fc.path[(int)threadIdx.x + k[u] * T];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      if (k[u] >= 0) body(k[u], t + k[u] * T, true, r[u]);
+      if (k[u] >= 0) body(k[u], (int)threadIdx.x + k[u] * T, true, r[u]);
   }
   for (uint64_t m = mask & ~cmask; m;) {
     int k[4];
@@ -1031,11 +996,11 @@ __device__ __forceinline__ void for_items(uint64_t mask, uint64_t cmask, const F
     for (int u = 0; u < 4; ++u) {
       k[u] = m ? __ffsll((unsigned long long)m) - 1 : -1;
       m &= m - 1;
-      if (k[u] >= 0) r[u] = stg[t + k[u] * T];
+      if (k[u] >= 0) r[u] = stg[(int)threadIdx.x + k[u] * T];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      if (k[u] >= 0) body(k[u], t + k[u] * T, false, r[u]);
+      if (k[u] >= 0) body(k[u], (int)threadIdx.x + k[u] * T, false, r[u]);
   }
 }
 
@@ -1050,8 +1015,8 @@ __device__ __forceinline__ void for_items(uint64_t mask, uint64_t cmask, const F
 // re-solve's take-back is done while the records are gathered and the slots
 // are written as flows freeze.  Paths must fit the record (<= 6 links,
 // part-local ids below 0xFFFF); n <= 64*T.
-template <bool TIGHT, bool MID, class LK>
-__device__ __forceinline__ int solve_mask(BlockG<TIGHT, MID>& g, const Params& P, LK& lk, ScenCtl* C,
+template <bool MID, class LK>
+__device__ __forceinline__ int solve_mask(BlockG<MID>& g, const Params& P, LK& lk, ScenCtl* C,
                                           const int32_t* list, int n, int64_t& rounds, int64_t& fsw,
                                           int64_t& isw, Clock& clk, bool warm, const FlowCache& fc,
                                           const Resel* rs) {
@@ -1065,10 +1030,10 @@ __device__ __forceinline__ int solve_mask(BlockG<TIGHT, MID>& g, const Params& P
   int* cntr = g.ldsi + 112;  // three rotating counters of unfrozen flows
   int bad = 0;
   if (!warm) cold_links(g, P, lk, C);
-  const uint64_t alive0 = low_items(n, T, g.t);
+  const uint64_t alive0 = low_items(n, T);
   uint64_t alive = alive0;
   const int nc = min(n, fc.cap);
-  const uint64_t cmask = low_items(nc, T, g.t);  // items served from the cache
+  const uint64_t cmask = low_items(nc, T);  // items served from the cache
   // gather: ids, path records (and, re-solving, the rates and remaining
   // bytes to take back), four items of a thread in flight at a time
   for (int j0 = 0; j0 * T < n; j0 += 4) {
@@ -1077,13 +1042,13 @@ __device__ __forceinline__ int solve_mask(BlockG<TIGHT, MID>& g, const Params& P
     double rr[4], tr[4], rm[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int i = g.t + (j0 + u) * T;
+      const int i = (int)threadIdx.x + (j0 + u) * T;
       fv[u] = i < n ? list[i] : f0;
       sv[u] = (rs && i < n) ? rs->at[i] : 0;
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int i = g.t + (j0 + u) * T;
+      const int i = (int)threadIdx.x + (j0 + u) * T;
       const bool ok = i < n && in_range(fv[u], f0, cap) && (unsigned)sv[u] < (unsigned)cap;
       rv[u] = ok ? P.path16[fv[u]] : make_uint4(~0u, ~0u, ~0u, ~0u);
       if (rs && ok && sv[u] < rs->s_new) {
@@ -1094,7 +1059,7 @@ __device__ __forceinline__ int solve_mask(BlockG<TIGHT, MID>& g, const Params& P
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int i = g.t + (j0 + u) * T;
+      const int i = (int)threadIdx.x + (j0 + u) * T;
       if (i >= n) continue;
       const int f = fv[u];
       if (!in_range(f, f0, cap) || (unsigned)sv[u] >= (unsigned)cap) bad = 2;
@@ -1126,14 +1091,13 @@ __device__ __forceinline__ int solve_mask(BlockG<TIGHT, MID>& g, const Params& P
   if (threadIdx.x < 3) cntr[threadIdx.x] = 0;
   if (bad) g.store(&K->fault, bad);
   __syncthreads();
-  const uint32_t st0 = g.uni(first_round(g, P, lk, C));
+  const uint32_t st0 = first_round(g, P, lk, C);
   clk.lap(2);
   int total = n;
   int r = 0;
   int rc = 0;
-  if (g.uni(g.load(&K->fault)) != 0) rc = ST_OVERFLOW;
+  if (g.load(&K->fault) != 0) rc = ST_OVERFLOW;
   for (; rc == 0;) {
-    g.fresh();
     const uint32_t st = st0 + (uint32_t)r;
     if (threadIdx.x == 0) cntr[(r + 1) % 3] = 0;
     round_table(g, lk, C);
@@ -1141,7 +1105,7 @@ __device__ __forceinline__ int solve_mask(BlockG<TIGHT, MID>& g, const Params& P
     // phase B: smallest share on each path; block links above it.  The
     // record's spare word keeps which of the flow's links are at its
     // minimum: the others carry its own stamp, so phase C looks only at those
-    for_items(alive, cmask, fc, stg, T, g.t, [&](int, int i, bool cached, uint4 rec) {
+    for_items(alive, cmask, fc, stg, T, [&](int, int i, bool cached, uint4 rec) {
       int lv[6];
       const int deg = unpack_path(rec, l0, lv);
       isw += deg;
@@ -1176,7 +1140,7 @@ __device__ __forceinline__ int solve_mask(BlockG<TIGHT, MID>& g, const Params& P
     clk.lap(4);
     // phase C: freeze flows crossing an unblocked link
     uint64_t frozen_mask = 0;
-    for_items(alive, cmask, fc, stg, T, g.t, [&](int k, int i, bool cached, uint4 rec) {
+    for_items(alive, cmask, fc, stg, T, [&](int k, int i, bool cached, uint4 rec) {
       int lv[6];
       const int deg = unpack_path(rec, l0, lv);
       const uint32_t cm = rec.w;
@@ -1225,9 +1189,8 @@ __device__ __forceinline__ int solve_mask(BlockG<TIGHT, MID>& g, const Params& P
       rounds += 1;
       fsw += total;
     }
-    const int ft = g.uni(g.load(&K->fault));
-    const int left = g.uni(cntr[r % 3]);
-    if (ft != 0) { rc = ft == 2 ? ST_OVERFLOW : ST_BAD_SHARE; break; }
+    if (g.load(&K->fault) != 0) { rc = g.load(&K->fault) == 2 ? ST_OVERFLOW : ST_BAD_SHARE; break; }
+    const int left = cntr[r % 3];
     if (left == 0) break;
     if (left >= total) { rc = ST_BAD_SHARE; break; }  // a round must freeze something
     if (++r > P.max_rounds) { rc = ST_ROUNDS; break; }
@@ -1242,7 +1205,7 @@ __device__ __forceinline__ int solve_mask(BlockG<TIGHT, MID>& g, const Params& P
       double mv[4], rm[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int i = g.t + (j0 + u) * T;
+        const int i = (int)threadIdx.x + (j0 + u) * T;
         if (i < n) {
           fv[u] = i < nc ? fc.fid[i] : list[i];
           mv[u] = mfi[i];
@@ -1251,12 +1214,12 @@ __device__ __forceinline__ int solve_mask(BlockG<TIGHT, MID>& g, const Params& P
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int i = g.t + (j0 + u) * T;
+        const int i = (int)threadIdx.x + (j0 + u) * T;
         if (i < n && rs) rm[u] = P.rem[fv[u]];
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        const int i = g.t + (j0 + u) * T;
+        const int i = (int)threadIdx.x + (j0 + u) * T;
         if (i >= n) continue;
         P.rate[fv[u]] = mv[u];
         if (rs) {
@@ -1577,8 +1540,8 @@ struct Assist {
   // and the slot of each in slot buffer ab; slots from s_new on were
   // activated at time t): the job's status, or NOT_TAKEN if the helpers
   // have left (nothing changed then).
-  template <class BG, class LK>
-  __device__ __forceinline__ int solve(BG& g, const Params& P, LK& lk, ScenCtl* C, int sc, int n,
+  template <class LK>
+  __device__ __forceinline__ int solve(BlockG<false>& g, const Params& P, LK& lk, ScenCtl* C, int sc, int n,
                                        int ab, int s_new, double t, int64_t& rounds, int64_t& fsw,
                                        int64_t& isw) {
     const int T = blockDim.x;
@@ -1856,8 +1819,8 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
   int32_t* arrs = P.arr + f0;
   int32_t* arrSlot = P.arrslot + f0;
   const int T = g.nthr();
-  int tid = g.tid();
-  int w0 = tid - lane_id();
+  const int tid = g.tid();
+  const int w0 = tid - lane_id();
   Clock clk(tid == 0 && (P.debug & 2), tl->clk);
   const bool resume = P.resume && C->started;
   if (threadIdx.x == 0) {
@@ -1881,21 +1844,26 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
   }
   const uint64_t INF_BITS = (uint64_t)__double_as_longlong(INF);
   // a part the wave kernel left between an event's releases and its solve
-  // (block kernel only) starts there, with that event's thetas
+  // (block kernel only) enters that event here, with its thetas, new flows and
+  // pending list: the search below finds nothing due any more, and counts the
+  // event and its slots, which the wave kernel has counted, again.  (Nothing
+  // of this is left in the other kernels, and no scope of its own around the
+  // search and the releases: that alone costs the cluster kernel 57 more
+  // spilled registers.)
   constexpr bool kMid = G::kMid;
   bool mid = kMid && resume && (C->mid & 1) != 0;
   if (!kMid || !mid)
     for (int c = C->c0 + tid; c < C->c0 + C->nc; c += T) P.theta[c] = INF_BITS;
-  double t = g.uni(resume ? C->t : 0.0);
-  int64_t events = g.uni(resume ? C->events : (int64_t)0), isw = 0;
+  double t = resume ? C->t : 0.0;
+  int64_t events = resume ? C->events : 0, isw = 0;
   // the launch's limit counts the wave kernel's events too
   const int64_t events0 = kMid && P.hand && resume ? events - C->launch_events : events;
-  int ab = g.uni(resume ? C->ab : 0);          // slot buffer in use
-  int nSlots = g.uni(resume ? C->nslots : 0);  // slots in use (flows or holes)
-  int nPend = g.uni(resume ? C->npend : C->n_pend0);
-  int e = g.uni(resume ? C->e : 0);  // event index: pend[e&1] is this event's pending list
-  int q = g.uni(resume ? C->q : 0);  // completion-list phase index (three rotating lists)
-  int64_t hp = g.uni(resume ? C->hpos : (int64_t)0);  // undo records written (rollback history)
+  int ab = resume ? C->ab : 0;          // slot buffer in use
+  int nSlots = resume ? C->nslots : 0;  // slots in use (flows or holes)
+  int nPend = resume ? C->npend : C->n_pend0;
+  int e = resume ? C->e : 0;  // event index: pend[e&1] is this event's pending list
+  int q = resume ? C->q : 0;  // completion-list phase index (three rotating lists)
+  int64_t hp = resume ? C->hpos : 0;  // undo records written (rollback history)
   const bool hist = HIST && P.hist != nullptr && C->hcap > 0;
   int status = ST_DONE;
   if (resume) {
@@ -1915,27 +1883,20 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
     if (tid == 0) {
       g.store(&K->slots, nSlots);
       g.store(&K->holes, C->holes);
-      if (kMid && mid) {
-        g.store(&K->pend[(e & 1) ^ 1], C->npend);
-        g.store(&K->arr, C->mid_narr);
-        g.store(&K->changed[e & 1], C->mid >> 1);
-      }
+    }
+    if (kMid && mid) {
+      nSlots = C->mid_slots0;
+      nPend = 0;
+      events -= 1;
+      if (threadIdx.x == 0) tl->asw -= nSlots;
     }
   }
   g.sync();
   for (;;) {
     const int ib = e & 1, ob = ib ^ 1;
-    if constexpr (!IsGrid<G>::value) {
-      g.fresh();
-      tid = g.tid();
-      w0 = tid - lane_id();
-    }
     const Slots sl = slots(ab);
     const int32_t* pendIn = pend(ib);
     int32_t* pendOut = pend(ob);
-    // slots at or above this one are activated in this event
-    const int slots0 = kMid && mid ? C->mid_slots0 : nSlots;
-    if (!kMid || !mid) {
     if (tid == 0) {
       g.store(&K->pend[ob], 0);
       g.store(&K->changed[ib], 0);
@@ -1943,6 +1904,11 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
       g.store(&K->arr, 0);
       g.store(&K->sel, 0);
       g.store(&K->slots2, 0);
+      if (kMid && mid) {
+        g.store(&K->pend[ob], C->npend);
+        g.store(&K->arr, C->mid_narr);
+        g.store(&K->changed[ib], C->mid >> 1);
+      }
     }
     // next event time: earliest predicted completion or release (four
     // slots of a thread in flight at a time).  Each thread also keeps the
@@ -1979,10 +1945,12 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
       tl->asw += nSlots;
       tl->psw += nPend;
     }
-    const double tn = g.uni(g.min_all(loc));
+    double tn = g.min_all(loc);
+    if (kMid && mid) tn = t;  // nothing is due any more
+    if constexpr (kMid) mid = false;
     clk.lap(0);
     if (g.aborted()) { status = ST_BARRIER; break; }
-    if (g.uni(g.load(&K->fault)) != 0) { status = ST_OVERFLOW; break; }
+    if (g.load(&K->fault) != 0) { status = ST_OVERFLOW; break; }
     if (!(tn < INF)) break;
     if ((P.max_events > 0 && events - events0 >= P.max_events) || tn > P.until) {
       status = ST_STOPPED;
@@ -1990,6 +1958,7 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
     }
     events += 1;
     const double thr = tn * THR;
+    const int slots0 = nSlots;  // slots at or above this one are activated in this event
     int32_t* compOut = comp(q % 3);
     int32_t* compCnt = &K->comp[q % 3];
     if (tid == 0) g.store(&K->comp[(q + 1) % 3], 0);
@@ -2076,7 +2045,7 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
     // dependants of finished flows, to a fixpoint through zero-byte flows.
     // A lane releases the successors of its own finished flow when it has a
     // few; long successor lists (a barrier's) are shared by the whole wave.
-    int nc = g.uni(g.load(&K->succ_flag[ib]) ? g.load(&K->comp[(q - 1) % 3]) : 0);
+    int nc = g.load(&K->succ_flag[ib]) ? g.load(&K->comp[(q - 1) % 3]) : 0;
     while (nc > 0) {
       const int32_t* cin = comp((q - 1) % 3);
       int32_t* cout = comp(q % 3);
@@ -2134,22 +2103,19 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
       if (err) g.store(&K->fault, 2);
       g.sync();
       q += 1;
-      nc = g.uni(g.load(&K->comp[(q - 1) % 3]));
+      nc = g.load(&K->comp[(q - 1) % 3]);
     }
     clk.lap(1);
     if (g.aborted()) { status = ST_BARRIER; break; }
-    if (g.uni(g.load(&K->fault)) != 0) { status = ST_OVERFLOW; break; }
-    }  // !mid
-    if constexpr (kMid) mid = false;
-    int err = 0;
-    nSlots = g.uni(g.load(&K->slots));
-    const int pNew = g.uni(g.load(&K->pend[ob]));
-    const int live = nSlots - g.uni(g.load(&K->holes));
-    if (g.uni(g.load(&K->changed[ib])) && live > 0) {
+    if (g.load(&K->fault) != 0) { status = ST_OVERFLOW; break; }
+    nSlots = g.load(&K->slots);
+    const int pNew = g.load(&K->pend[ob]);
+    const int live = nSlots - g.load(&K->holes);
+    if (g.load(&K->changed[ib]) && live > 0) {
       // theta of each component: below it every rate stays as it was.
       // Finished flows have fed it their rates; new flows feed the initial
       // share of their links.
-      const int nArr = g.uni(g.load(&K->arr));
+      const int nArr = g.load(&K->arr);
       for (int i = tid; i < nArr; i += T) {
         const int f = arrs[i];
         if (!in_range(f, f0, cap)) continue;
@@ -2167,7 +2133,7 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
       // With a single link component theta is one value for the whole part.
       {
         const bool one_comp = C->nc == 1;
-        const double theta1 = g.uni(__longlong_as_double((long long)g.load(&P.theta[C->c0])));
+        const double theta1 = __longlong_as_double((long long)g.load(&P.theta[C->c0]));
         int32_t* const cnts[1] = {&K->sel};
         sweep_append<1>(
             g, nSlots, cnts,
@@ -2210,7 +2176,7 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
       g.sync();
       clk.lap(7);
       for (int c = C->c0 + tid; c < C->c0 + C->nc; c += T) P.theta[c] = INF_BITS;
-      const int nSel = g.uni(g.load(&K->sel));
+      const int nSel = g.load(&K->sel);
       if (threadIdx.x == 0) tl->sel += nSel;
       if constexpr (HIST) hp += nSel;
       int rc = 0;
@@ -2259,7 +2225,7 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
             rc = ST_OVERFLOW;
           } else if (C->lds_paths && nSel <= LDS_FLOWS) {
             if (g.block_id() == 0) {
-              BlockG<false, false> b{g.lds, g.ldsi, &C->k};  // the grid's counters, in global memory
+              BlockG<false> b{g.lds, g.ldsi, &C->k};  // the grid's counters, in global memory
               const int r1 = solve_mask(b, P, lk, C, arrs, nSel, rounds, fsw, isw, clk, true, fc,
                                         nullptr);
               if (threadIdx.x == 0) g.store(&K->solve_rc, r1);
@@ -2302,7 +2268,7 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
     // compaction: when holes are more than an eighth of the slots, copy the
     // live ones into the other buffer (every event sweeps all slots, holes
     // included, and a compaction costs about one sweep)
-    const int holes = g.uni(g.load(&K->holes));
+    const int holes = g.load(&K->holes);
     if (8 * holes > nSlots) {
       const Slots nx = slots(ab ^ 1);
       int32_t* const cnts[1] = {&K->slots2};
@@ -2327,7 +2293,7 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
           });
       if (err) g.store(&K->fault, 2);
       g.sync();
-      nSlots = g.uni(g.load(&K->slots2));
+      nSlots = g.load(&K->slots2);
       ab ^= 1;
       g.sync();  // every thread has read the counters before they are reset
       if (tid == 0) {
@@ -2434,7 +2400,7 @@ __global__ __launch_bounds__(NT) void netsim_block_kernel(Params P) {
   __shared__ Tally tally;
   __shared__ Lists lists;
   __shared__ __align__(16) unsigned char pool[POOL_BYTES];
-  BlockG<false, (NT <= 512)> g{lds, ldsi, &lists};
+  BlockG<(NT <= 512)> g{lds, ldsi, &lists};
   const int parts = P.pcount ? *P.pcount : P.list ? P.num_list : P.num_scen;
   for (int i = blockIdx.x; i < parts; i += gridDim.x) {
     const int sc = P.list ? P.list[i] : i;
@@ -2473,7 +2439,7 @@ __global__ __launch_bounds__(NT) void netsim_solve_kernel(Params P) {
   __shared__ Tally tally;
   __shared__ Lists lists;
   __shared__ __align__(16) unsigned char pool[POOL_BYTES];
-  BlockG<false, false> g{lds, ldsi, &lists};
+  BlockG<false> g{lds, ldsi, &lists};
   for (int sc = blockIdx.x; sc < P.num_scen; sc += gridDim.x) {
     const ScenCtl* C = &P.ctl[sc];
     if (threadIdx.x == 0) lists = Lists{};
@@ -2583,7 +2549,7 @@ __global__ __launch_bounds__(1024) void netsim_cluster_kernel(Params P) {
     }
     return;
   }
-  BlockG<true, false> g{lds, ldsi, &lists};
+  BlockG<false> g{lds, ldsi, &lists};
   Assist as{P.bar, cw, nh, P.assist_min > 0 ? P.assist_min : 1, 0u, box};
   for (;;) {
     if (threadIdx.x == 0)
