@@ -825,6 +825,25 @@ netsim_status reset_state(netsim_t* h, hipStream_t st) {
   return he == hipSuccess ? NETSIM_OK : hip_fail(h, he, "reset of the state");
 }
 
+// The stream for work beside the caller's, and its events: all or none.
+hipError_t side_stream(netsim_t* h) {
+  if (h->side) return hipSuccess;
+  hipStream_t s = nullptr;
+  hipEvent_t ev[2] = {};
+  hipError_t he = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+  for (auto& e : ev)
+    if (he == hipSuccess) he = hipEventCreateWithFlags(&e, hipEventDisableTiming);
+  if (he == hipSuccess) {
+    h->side = s;
+    std::copy(ev, ev + 2, h->side_ev);
+    return hipSuccess;
+  }
+  for (hipEvent_t e : ev)
+    if (e) (void)hipEventDestroy(e);
+  if (s) (void)hipStreamDestroy(s);
+  return he;
+}
+
 // The block layout's (or exact mode's) event loops: the small parts one
 // wavefront each, the others one workgroup each beside them (on a stream of
 // the handle's own, joined before the launch ends), then the parts the wave
@@ -835,11 +854,7 @@ hipError_t launch_event_loops(netsim_t* h, const Params& P0, hipStream_t st, con
   Params P = P0;
   hipError_t he = hipSuccess;
   if (h->big_count > 0) {
-    if (!h->side) {
-      he = hipStreamCreateWithFlags(&h->side, hipStreamNonBlocking);
-      for (auto& ev : h->side_ev)
-        if (he == hipSuccess) he = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-    }
+    he = side_stream(h);
     if (he == hipSuccess) he = hipEventRecord(h->side_ev[0], st);
     if (he == hipSuccess) he = hipStreamWaitEvent(h->side, h->side_ev[0], 0);
     P.list = h->d_plist + h->big_first;
@@ -911,9 +926,8 @@ netsim_status launch(netsim_t* h, hipStream_t st, bool solve_only, float* ms, bo
   // grid-barrier words and min-reduction slots start fresh in every launch
   // (a launch that continues a run must not see the last launch's counts)
   hipError_t he = netsim_dev::launch_reset_words(P, h->res, (int)h->scen.size(), st);
-  if (he != hipSuccess) return hip_fail(h, he, "reset of the grid synchronisation words");
   const hipEvent_t e0 = h->ev[0], e1 = h->ev[1];
-  he = hipEventRecord(e0, st);
+  if (he == hipSuccess) he = hipEventRecord(e0, st);
   if (he == hipSuccess) {
     if (exec == NETSIM_EXEC_EXACT) {
       // link state in shared memory for every part whose links fit the pool
@@ -990,8 +1004,12 @@ netsim_status launch(netsim_t* h, hipStream_t st, bool solve_only, float* ms, bo
   }
   if (he == hipSuccess) he = hipEventSynchronize(e1);
   if (he == hipSuccess) he = hipEventElapsedTime(ms, e0, e1);
-  if (he != hipSuccess) return hip_fail(h, he, "kernel launch");
-  return NETSIM_OK;
+  if (he == hipSuccess) return NETSIM_OK;
+  // what was queued before the failure ends before the call returns: the
+  // state it works on is the caller's next call's, on whichever stream
+  if (h->side) (void)hipStreamSynchronize(h->side);
+  (void)hipStreamSynchronize(st);
+  return hip_fail(h, he, "kernel launch");
 }
 
 netsim_status collect(netsim_t* h, std::vector<ScenCtl>* ctl_out) {

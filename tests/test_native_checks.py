@@ -12,12 +12,15 @@ CPU (no GPU: device code is not instrumented).
   solve (the gather, both phases of a freezing round, the write-back) runs
   at every number of path records in flight per thread from 1 to 8 over
   re-solve sizes of the 4096-GPU workload.
+* The host side of libnetsim on a stand-in runtime, every runtime call and
+  kernel launch of a run made to fail in turn (host_failures.cpp).
 
 Every check must report no error; sanitizer reports make the subprocess fail.
 """
 
 import glob
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -55,6 +58,20 @@ def test_solve_mask_index_model(tmp_path):
     out = _run([exe], env=_env(""))
     for d in range(1, 9):
         assert f"depth {d}: 132 cases, in bounds" in out, out
+
+
+@pytest.mark.parametrize("mode", ["join"])
+def test_host_failures(tmp_path, mode):
+    exe = str(tmp_path / "host_failures")
+    native = os.path.join(ROOT, "tests", "native")
+    csrc = os.path.join(ROOT, "paper_2505_01616_amd", "csrc")
+    _run(["g++", "-O1", "-g", "-std=c++17", "-Wall", "-fsanitize=address,undefined",
+          "-fno-sanitize-recover=undefined", "-I", os.path.join(native, "runtime"),
+          "-I", os.path.join(ROOT, "include"), "-I", csrc, "-o", exe, os.path.join(native, "host_failures.cpp"),
+          os.path.join(csrc, "netsim.cpp"), os.path.join(csrc, "fabric.cpp")])
+    out = _run([exe, mode], env=_env(""))
+    tried = re.search(mode + r": (\d+) failures tried, 0 wrong", out)
+    assert tried and int(tried.group(1)) > 150, out
 
 
 def test_oracle_under_sanitizers(tmp_path):
