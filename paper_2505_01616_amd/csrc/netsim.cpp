@@ -314,7 +314,32 @@ constexpr size_t kWaveClassBytes[] = {6 * 1024, 20 * 1024, 150 * 1024};
 constexpr int DEBUG_EXACT_GLOBAL = 16;  // options.debug bit 4: exact link state in global memory
 constexpr int DEBUG_EXACT_GRID = 32;  // options.debug bit 5: every such solve on the whole GPU
 
-netsim_status prepare(netsim_t* h) {
+void drop_checkpoints(netsim_t* h) {
+  for (auto& c : h->checkpoints)
+    if (c.dev) (void)hipFree(c.dev);
+  h->checkpoints.clear();
+}
+
+// Gives back everything the handle holds on the device.
+void release_device(netsim_t* h) {
+  drop_checkpoints(h);
+  for (auto* events : {h->side_ev, h->ev})
+    for (int k = 0; k < 2; ++k) {
+      if (events[k]) (void)hipEventDestroy(events[k]);
+      events[k] = nullptr;
+    }
+  if (h->side) (void)hipStreamDestroy(h->side);
+  h->side = nullptr;
+  if (h->host_pinned) (void)hipHostFree(h->host);
+  else delete[] h->host;
+  h->host = nullptr;
+  h->host_pinned = false;
+  if (h->d_block) (void)hipFree(h->d_block);
+  if (h->d_hist) (void)hipFree(h->d_hist);
+  h->d_block = h->d_hist = nullptr;
+}
+
+netsim_status prepare_device(netsim_t* h) {
   const int32_t S = (int32_t)h->scen.size();
   const int64_t F = (int64_t)h->f_bytes.size();
   h->F = F;
@@ -817,6 +842,16 @@ netsim_status prepare(netsim_t* h) {
   return NETSIM_OK;
 }
 
+// The device layout of the handle's flows, made by its first run or rate solve.
+netsim_status prepare(netsim_t* h) {
+  const netsim_status rc = prepare_device(h);
+  if (rc != NETSIM_OK) {  // the next call prepares again
+    release_device(h);
+    (void)hipGetLastError();
+  }
+  return rc;
+}
+
 // Resets the dynamic state for a run from t = 0 (on `stream`, in its order).
 netsim_status reset_state(netsim_t* h, hipStream_t st) {
   h->hist_ok = h->prm.hist != nullptr;
@@ -1035,13 +1070,6 @@ netsim_status collect(netsim_t* h, std::vector<ScenCtl>* ctl_out) {
     }
   }
   return NETSIM_OK;
-}
-
-
-void drop_checkpoints(netsim_t* h) {
-  for (auto& c : h->checkpoints)
-    if (c.dev) (void)hipFree(c.dev);
-  h->checkpoints.clear();
 }
 
 // A fresh run from t = 0 (resume = false) or a continuation of the current
@@ -2392,16 +2420,7 @@ void netsim_destroy(netsim_t* h) {
   if (!h) return;
   if (h->d_block) {
     (void)hipSetDevice(h->opt.device);
-    drop_checkpoints(h);
-    for (hipEvent_t ev : h->side_ev)
-      if (ev) (void)hipEventDestroy(ev);
-    if (h->side) (void)hipStreamDestroy(h->side);
-    for (hipEvent_t ev : h->ev)
-      if (ev) (void)hipEventDestroy(ev);
-    if (h->host_pinned) (void)hipHostFree(h->host);
-    else delete[] h->host;
-    (void)hipFree(h->d_block);
-    if (h->d_hist) (void)hipFree(h->d_hist);
+    release_device(h);
   }
   delete h;
 }

@@ -60,7 +60,7 @@ def test_solve_mask_index_model(tmp_path):
         assert f"depth {d}: 132 cases, in bounds" in out, out
 
 
-@pytest.mark.parametrize("mode", ["join"])
+@pytest.mark.parametrize("mode", ["join", "keep"])
 def test_host_failures(tmp_path, mode):
     exe = str(tmp_path / "host_failures")
     native = os.path.join(ROOT, "tests", "native")
