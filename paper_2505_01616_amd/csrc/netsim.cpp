@@ -1160,7 +1160,11 @@ netsim_status grid_solve(netsim_t* h, hipStream_t st, int32_t p, int32_t n, Grid
   const int64_t limit = h->opt.max_rounds > 0 ? h->opt.max_rounds : (int64_t)n + 1;
   netsim_dev::XGridHead g{};  // the counters the host reads
   if (netsim_dev::grid_solve_fill_fits(C) && (h->opt.debug & DEBUG_EXACT_GRID) == 0) {
-    if (he == hipSuccess) he = netsim_dev::grid_solve_fill(P, C, n, (int)std::min<int64_t>(limit, INT32_MAX), st);
+    // (the sweeps look at the watchdog after levels 2, 66, 130, ...: a solve
+    // wide enough for them may use the levels up to the next look here too)
+    int64_t most = limit;
+    if (n >= kExactGridMin) most = limit < 2 ? 1 : ((limit - 2) / kGridLevelBatch + 1) * kGridLevelBatch + 1;
+    if (he == hipSuccess) he = netsim_dev::grid_solve_fill(P, C, n, (int)std::min<int64_t>(most, INT32_MAX), st);
     unsigned long long isw = 0, lsw = 0;
     if (he == hipSuccess) he = hipMemcpyAsync(&g, P.xgrid, sizeof g, hipMemcpyDeviceToHost, st);
     if (he == hipSuccess) he = hipMemcpyAsync(&isw, P.xgrid->isw, sizeof isw, hipMemcpyDeviceToHost, st);

@@ -112,3 +112,36 @@ def test_exact_by_links(links, flows, deg, equal):
         torch.cuda.synchronize()
         assert status.tolist() == [ns.OK, stats[0][0]]
         assert np.array_equal(rates.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("levels,limit,ok", [(1, 1, True), (2, 1, False), (8, 2, True), (65, 2, True), (66, 2, False),
+                                             (66, 66, True), (129, 66, True), (130, 66, False)])
+def test_exact_watchdog_of_wide_solves(levels, limit, ok):
+    """max_rounds in an exact solve of 16,384 flows and more is looked at after
+    levels 2, 66, 130, ...: a solve that ends before the next look passes,
+    by links as on the whole GPU (debug bit 5)."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2505_01616_amd import netsim as ns
+    from paper_2505_01616_amd import program as prog
+    print(f"test_exact_watchdog levels={levels} limit={limit}", file=sys.stderr, flush=True)
+    flows = 16384
+    caps = 100.0 + np.arange(levels)  # a flow crosses one link: a level per link
+    sc = Scenario(Topology(kind="explicit", capacities=caps))
+    for i in range(flows):
+        sc.add(PathFlow([i % levels], 1.0))
+    count = np.bincount(np.arange(flows) % levels)
+    assert len(np.unique(caps / count)) == levels
+    for debug in (0, 32):
+        ld = prog.load_program(Program("watchdog", [sc]), ns.make_options(exact=1, max_rounds=limit, debug=debug))
+        try:
+            if ok:
+                got = ns.netsim_solve_once(ld.handle, 0, np.arange(flows))
+                assert np.array_equal(got, (caps / count)[np.arange(flows) % levels])
+                assert ns.netsim_get_stats(ld.handle)["rounds"] == levels
+            else:
+                with pytest.raises(ns.NetsimError, match="watchdog"):
+                    ns.netsim_solve_once(ld.handle, 0, np.arange(flows))
+        finally:
+            ld.close()
