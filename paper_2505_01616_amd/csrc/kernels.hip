@@ -2345,7 +2345,8 @@ __device__ __forceinline__ void event_loop(G& g, const Params& P, LK& lk, const 
     if constexpr (kMid) C->mid = 0;
     C->launch_events = events - events0;
     C->status = status;
-    for (int k = 0; k < 8; ++k) C->ticks[k] = (int64_t)tl->clk[k];
+    // (after the wave kernel's, in a part it handed over in this launch)
+    for (int k = 0; k < 8; ++k) C->ticks[k] = (kMid && P.hand ? C->ticks[k] : 0) + (int64_t)tl->clk[k];
   }
 }
 

@@ -519,6 +519,7 @@ __device__ __forceinline__ void wave_loop(const Params& P, int part, int sc, int
   if (!w.load(resume)) {  // more than the lists hold: the block kernel's from here
     if (lane == 0) {
       C->launch_events = 0;
+      for (int k = 0; k < 8; ++k) C->ticks[k] = 0;
       P.hlist[__hip_atomic_fetch_add(P.hcount, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = part;
     }
     return;

@@ -197,3 +197,22 @@ def test_many_ends_followed_by_lags(n, latency):
     for k in SAME:
         assert sb[k] == sc[k], (k, sb[k], sc[k])
     assert np.max(np.abs(b[0] - want.finish) / want.finish) < 1e-9
+
+
+def test_phase_times_of_a_part_handed_over():
+    """The phase timers count both kernels' time: 400 flows one after another
+    in the one-wave kernel, then 300 at once, which it hands over."""
+    ns, pr = _gpu()
+    _say("test_phase_times_of_a_part_handed_over")
+    sc = Scenario(Topology(kind="explicit", capacities=np.full(8, 4.0)))
+    last = sc.add(PathFlow([0], 1.0))
+    for i in range(400):
+        last = sc.add(PathFlow([i % 8], 1.0 + i % 3, after=(last,)))
+    for i in range(300):
+        sc.add(PathFlow([i % 8], 2.0, after=(last,)))
+    program = Program("phases", [sc])
+    _, s = pr.run_program(program, ns.make_options(debug=2))
+    _, t = pr.run_program(program, ns.make_options())
+    assert s["events"] == t["events"] >= 402
+    # most of the run is in a phase (the rest: reading and writing positions)
+    assert sum(s["phase_seconds"]) > 0.5 * s["device_seconds"], (s["phase_seconds"], s["device_seconds"])
