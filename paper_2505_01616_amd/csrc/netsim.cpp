@@ -299,15 +299,21 @@ constexpr int kCusPerXcd = 32;
 // to 6,485 links per part) and threads per workgroup.
 constexpr int64_t kExactLdsBytes = 152 * 1024;
 constexpr int kExactThreads = 512;
-// Exact mode: a rate solve without an event loop of at least this many flows
-// runs on the whole GPU (sweep.hip) instead of one workgroup; levels are
-// enqueued this many at a time between looks at the unfrozen count.
+// Exact mode: a rate solve without an event loop of at least kExactGridMin
+// flows, or kExactFillMin where its links fit the solve by links (the line
+// measured for device arrays, NA_INDEX_MIN in exact.hip), starts on the whole
+// GPU (sweep.hip) instead of in one workgroup.  Levels swept on the whole GPU
+// are enqueued kGridLevelBatch at a time between looks at the unfrozen count.
 constexpr int32_t kExactGridMin = 16384;
 constexpr int32_t kExactFillMin = 1024;
 constexpr int kGridLevelBatch = 64;
 constexpr size_t kPinnedMin = 256 * 1024;  // results at least this long are copied to pinned memory
 // Wave kernel: room for active and pending flows at most, and the classes of
-// parts by shared memory (26, 8 or fewer parts on a compute unit at once).
+// parts by the shared memory their own links and lists take.  A class's lists
+// are as long as its widest part's, so a launch may take a little more.  Parts
+// of the first class have a compute unit's registers as their limit (12 at
+// once, in exact mode 8), those of the second its shared memory (up to 8),
+// the others run a few or one at a time.
 constexpr int32_t kWaveSlots = 256, kWavePending = 512;
 constexpr int32_t kXWaveSlots = 512;  // exact mode (its solve's registers hold 8 x 64 flows)
 constexpr size_t kWaveClassBytes[] = {6 * 1024, 20 * 1024, 150 * 1024};

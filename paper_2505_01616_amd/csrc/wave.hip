@@ -20,7 +20,8 @@
 //   - the links an event's re-solve touches are listed, so a freezing round
 //     looks at those links only;
 //   - a part takes a few kB of shared memory instead of the whole pool, so
-//     a compute unit runs up to 16 parts at once instead of one.
+//     a compute unit runs up to 12 parts at once (149 registers per lane: three
+//     waves a SIMD) instead of one.
 // Measured (one pass through the C ABI, before: every part in the block kernel):
 // ring all-reduce of 64 GPUs 12.0 -> 4.8 ms (981 events), 3D-parallel step on
 // 128 GPUs 4.7 -> 1.6 ms, training-step trace of 128 GPUs 252 -> 89 ms (22,872
