@@ -316,6 +316,11 @@ constexpr size_t kPinnedMin = 256 * 1024;  // results at least this long are cop
 // the others run a few or one at a time.
 constexpr int32_t kWaveSlots = 256, kWavePending = 512;
 constexpr int32_t kXWaveSlots = 512;  // exact mode (its solve's registers hold 8 x 64 flows)
+// ... but 448 for scenarios of more than 1,024 links, whose link pass outweighs
+// the barriers one wave saves: time of the workgroup kernel over the wave's with
+// 448 and 512 flows active 1.11 and 1.05 at 1,000 links (four a path), 1.06 and
+// 1.00 at 1,400, 0.98 and 0.92 at 2,800.
+constexpr int32_t kXWaveManyLinks = 1024, kXWaveSlotsMany = 448;
 constexpr size_t kWaveClassBytes[] = {6 * 1024, 20 * 1024, 150 * 1024};
 constexpr int DEBUG_EXACT_GLOBAL = 16;  // options.debug bit 4: exact link state in global memory
 constexpr int DEBUG_EXACT_GRID = 32;  // options.debug bit 5: every such solve on the whole GPU
@@ -650,7 +655,8 @@ netsim_status prepare_device(netsim_t* h) {
         real += nbytes[(size_t)d] > 0.0;
         roots += nbytes[(size_t)d] > 0.0 && ndeps[(size_t)d] == 0;
       }
-      const int32_t sc = std::min(real, exact ? kXWaveSlots : kWaveSlots), pc = std::min(c.f1 - c.f0, kWavePending);
+      const int32_t most = !exact ? kWaveSlots : c.l1 - c.l0 > kXWaveManyLinks ? kXWaveSlotsMany : kXWaveSlots;
+      const int32_t sc = std::min(real, most), pc = std::min(c.f1 - c.f0, kWavePending);
       const size_t z = wave_size(c, sc, pc);
       size_t q = 0;
       while (q < kClasses && z > kWaveClassBytes[q]) ++q;

@@ -216,3 +216,18 @@ def test_phase_times_of_a_part_handed_over():
     assert s["events"] == t["events"] >= 402
     # most of the run is in a phase (the rest: reading and writing positions)
     assert sum(s["phase_seconds"]) > 0.5 * s["device_seconds"], (s["phase_seconds"], s["device_seconds"])
+
+
+@pytest.mark.parametrize("n", [448, 449, 512])
+def test_exact_hand_over_with_many_links(n):
+    """Scenarios of more than 1,024 links leave the one-wave kernel at 448
+    active flows: bit for bit the oracle on both sides of the line."""
+    ns, pr = _gpu()
+    program = _release(n, False, links=4000)
+    used = {l for f in program.scenarios[0].ops if isinstance(f, PathFlow) for l in f.path}
+    _say(f"test_exact_hand_over_with_many_links n={n} links={len(used)}")
+    assert len(used) > 1024
+    want = osim.run_scenario(program.scenarios[0])
+    a, sa = pr.run_program(program, ns.make_options(exact=1))
+    assert np.array_equal(a[0], want.finish)
+    assert (sa["events"], sa["solves"], sa["rounds"]) == (want.events, want.solves, want.iterations)
