@@ -1104,7 +1104,12 @@ netsim_status simulate(netsim_t* h, hipStream_t st, bool resume, int64_t max_eve
   float ms = 0.0f;
   if (h->F > 0) {
     rc = launch(h, st, false, &ms, resume, max_events, until);
-    if (rc) return rc;
+    if (rc) {
+      // parts may have been left between the wave kernel and the launch that
+      // was to take them over: no position to go on from
+      h->has_state = false;
+      return rc;
+    }
   } else {
     he = hipStreamSynchronize(st);
     if (he != hipSuccess) return hip_fail(h, he, "hipStreamSynchronize (reset)");

@@ -1,11 +1,13 @@
 // The host side of libnetsim (netsim.cpp) with every runtime call and kernel
-// launch of a first and a second run made to fail in turn, on the stand-in
+// launch of a first run, a second run and an advance made to fail in turn, on the stand-in
 // runtime of tests/native/runtime (the launches only queue work).  After a
 // call that fails
 //   join   no work it queued is still running: the caller may use the
 //          handle's state on another stream at once;
-//   keep   the next call succeeds, and destroying the handle leaves no device
-//          or pinned memory, stream or event behind.
+//   keep   the next call succeeds, and does not go on from parts that the wave
+//          kernel left in the middle of an event for a launch that never came;
+//          destroying the handle leaves no device or pinned memory, stream or
+//          event behind.
 // Run by tests/test_native_checks.py.
 #include <hip/hip_runtime.h>
 
@@ -16,10 +18,25 @@
 
 FakeHip fake;
 
+// The wave kernel may have left parts in the middle of an event.
+static bool in_event = false;
+static hipError_t wave(hipStream_t s) {
+  if (in_event) FakeHip::bug("a part left in the middle of an event is run from its start");
+  const hipError_t e = fake.work(s);
+  in_event = e == hipSuccess;
+  return e;
+}
+static hipError_t workgroups(const netsim_dev::Params& P, hipStream_t s) {
+  const hipError_t e = fake.work(s);
+  if (e == hipSuccess && P.hand) in_event = false;
+  return e;
+}
+
 namespace netsim_dev {
 hipError_t launch_reset(const Params& P, const Initial& I, int64_t, int64_t, int NP, bool, hipStream_t s) {
   const hipError_t e = fake.work(s);
   if (e == hipSuccess) memcpy(P.ctl, I.ctl, sizeof(ScenCtl) * (size_t)NP);
+  if (e == hipSuccess) in_event = false;
   return e;
 }
 hipError_t launch_reset_words(const Params&, const Results&, int, hipStream_t s) { return fake.work(s); }
@@ -29,11 +46,11 @@ hipError_t launch_results(const Params&, const Results&, const int32_t*, const i
 }
 hipError_t launch_count_active(const Params&, const int32_t*, int, hipStream_t s) { return fake.work(s); }
 hipError_t launch_gather_rates(const Params&, const int32_t*, int, double*, hipStream_t s) { return fake.work(s); }
-hipError_t launch_block(const Params&, int, int, hipStream_t s) { return fake.work(s); }
+hipError_t launch_block(const Params& P, int, int, hipStream_t s) { return workgroups(P, s); }
 hipError_t launch_solve(const Params&, int, int, hipStream_t s) { return fake.work(s); }
-hipError_t launch_wave(const Params&, const int32_t*, int, int, int, size_t, hipStream_t s) { return fake.work(s); }
+hipError_t launch_wave(const Params&, const int32_t*, int, int, int, size_t, hipStream_t s) { return wave(s); }
 size_t wave_bytes(int nl, int, int sc, int pc) { return 38 * (size_t)nl + 76 * (size_t)sc + 12 * (size_t)pc; }
-hipError_t launch_xwave(const Params&, const int32_t*, int, int, int, size_t, hipStream_t s) { return fake.work(s); }
+hipError_t launch_xwave(const Params&, const int32_t*, int, int, int, size_t, hipStream_t s) { return wave(s); }
 size_t xwave_bytes(int nl, int sc, int pc) { return 34 * (size_t)nl + 62 * (size_t)sc + 12 * (size_t)pc; }
 hipError_t launch_grid(const Params&, int, int, hipStream_t s) { return fake.work(s); }
 hipError_t grid_capacity(int, int, int* blocks) {
@@ -45,7 +62,7 @@ hipError_t cluster_capacity(int, int* blocks) {
   *blocks = 256;
   return hipSuccess;
 }
-hipError_t launch_exact(const Params&, int, int, hipStream_t s) { return fake.work(s); }
+hipError_t launch_exact(const Params& P, int, int, hipStream_t s) { return workgroups(P, s); }
 hipError_t history_restore(const Params&, int, int, int, int64_t, int64_t, int32_t, const HistEv&, int64_t,
                            const int32_t*, const double*, int32_t*, uint32_t*, hipStream_t s) {
   return fake.work(s);
@@ -108,25 +125,27 @@ int main(int argc, char** argv) {
   for (const auto& m : modes) {
     netsim_options opt;
     netsim_default_options(&opt);
+    opt.single_clock = 1;  // one part a scenario: one launch of the wave kernel
     opt.exact = m.exact;
     opt.history_mb = m.history;
     opt.exec = m.exact ? NETSIM_EXEC_AUTO : NETSIM_EXEC_BLOCK;
-    for (int run = 0; run < 2; ++run)  // the first run (preparation), a later one
+    for (int run = 0; run < 3; ++run)  // the first run (preparation), a later one, a later advance
       for (long at = 1;; ++at) {
         fake.fail_at = 0;
         netsim_t* h = make(opt, m.wide);
         ihipStream own;
         fake.streams.insert(&own);
         if (run && netsim_run(h, &own) != NETSIM_OK) FakeHip::bug("a run without failures");
+        auto go = [&] { return run < 2 ? netsim_run(h, &own) : netsim_advance(h, 1e9, 0, &own); };
         fake.calls = 0;
         fake.fail_at = at;
-        const netsim_status rc = netsim_run(h, &own);
+        const netsim_status rc = go();
         const bool reached = fake.calls >= at;
         fake.fail_at = 0;
         if (join) {
           expect(fake.queued() == 0, "work still queued after the call", m.name, at);
         } else {
-          expect(netsim_run(h, &own) == NETSIM_OK, "the next run fails", m.name, at);
+          expect(go() == NETSIM_OK, "the next run fails", m.name, at);
           expect(fake.queued() == 0, "work still queued after the next run", m.name, at);
         }
         netsim_destroy(h);
@@ -137,6 +156,7 @@ int main(int argc, char** argv) {
         for (void* p : fake.device) free(p);
         for (void* p : fake.pinned) free(p);
         fake = FakeHip();
+        in_event = false;
         if (!reached) {
           if (rc != NETSIM_OK) FakeHip::bug("a run without failures");
           break;

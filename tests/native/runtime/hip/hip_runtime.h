@@ -85,7 +85,9 @@ hipError_t hipMalloc(T** p, size_t n) {
   fake.device.insert((void*)*p);
   return hipSuccess;
 }
-inline hipError_t hipFree(void* p) {
+inline hipError_t hipFree(void* p) {  // waits for the device
+  fake.wait(&fake.null_stream);
+  for (ihipStream* s : fake.streams) fake.wait(s);
   if (p && !fake.device.erase(p)) FakeHip::bug("device memory given back twice");
   free(p);
   return hipSuccess;
